@@ -149,7 +149,7 @@ def trace_summary(path, steps):
     candidates, the counting pass and the warm-up."""
     import csv
     with open(path) as f:
-        rows = [r for r in csv.DictReader(f) if "k_forward<false, 0, true, false>" in r["Kernel_Name"]]
+        rows = [r for r in csv.DictReader(f) if "k_forward<false, 0, true, false" in r["Kernel_Name"]]
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
     if len(rows) < 2 * steps:
         raise SystemExit("%s: %d forward dispatches, fewer than 2 x %d" % (path, len(rows), steps))

@@ -144,8 +144,9 @@ rt_status rt_scene_info_get(const rt_scene* scene, rt_scene_info* out);
  *                                   x_hi, y_lo, y_hi, z_lo, z_hi of children
  *                                   0..3, then the four child refs as int bits
  *                                   (>= 0 wide node, < 0 leaf slot ~r,
- *                                   0x7fffffff empty), then unused; node 0 is
- *                                   the root
+ *                                   0x7fffffff empty), then the leaf mask as
+ *                                   int bits (bit c + 1: child c is a leaf) and
+ *                                   three unused; node 0 is the root
  *   tris    float  [n_triangles][12] triangles in slot order: (v0, original
  *                                   id bits), (v1, material bits), (v2, 0)
  *   n_wide  out (may be NULL): number of 4-wide nodes, 0 if the scene has no

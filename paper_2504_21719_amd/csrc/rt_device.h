@@ -34,21 +34,19 @@ __device__ __forceinline__ cf cdiv(cf a, cf b) {
     float inv = __builtin_amdgcn_rcpf(cabs2(b));
     return cf{(a.re * b.re + a.im * b.im) * inv, (a.im * b.re - a.re * b.im) * inv};
 }
-// Principal square root (Re >= 0).  With m = |z|:
-//   Re >= 0 branch:  t = sqrt((m + x)/2),  sqrt(z) = t + j y/(2t)
-//   x < 0:           t = sqrt((m - x)/2),  sqrt(z) = |y|/(2t) + j sign(y) t
-// choosing the branch that avoids cancellation in m +- x.  Hardware square
-// root and reciprocal (about 1 ulp each).
+// Principal square root (Re >= 0).  With m = |z| and t = sqrt((m + |x|)/2):
+//   x >= 0:  sqrt(z) = t + j y/(2t)
+//   x < 0:   sqrt(z) = |y|/(2t) + j sign(y) t
+// so that m +- x never cancels.  Both are selected, not branched to.  Hardware
+// square root and reciprocal (about 1 ulp each).
 __device__ __forceinline__ cf csqrt_principal(cf z) {
-    float x = z.re, y = z.im;
-    float m = __builtin_amdgcn_sqrtf(x * x + y * y);
-    if (m == 0.0f) return cf{0.0f, 0.0f};
-    if (x >= 0.0f) {
-        float t = __builtin_amdgcn_sqrtf(0.5f * (m + x));
-        return cf{t, y * __builtin_amdgcn_rcpf(2.0f * t)};
-    }
-    float t = __builtin_amdgcn_sqrtf(0.5f * (m - x));
-    return cf{fabsf(y) * __builtin_amdgcn_rcpf(2.0f * t), copysignf(t, y)};
+    const float x = z.re, y = z.im;
+    const float m = __builtin_amdgcn_sqrtf(x * x + y * y);
+    const float t = __builtin_amdgcn_sqrtf(0.5f * (m + fabsf(x)));
+    const float h = y * __builtin_amdgcn_rcpf(2.0f * t);
+    const bool right = x >= 0.0f;
+    const cf r = cf{right ? t : fabsf(h), right ? h : copysignf(t, y)};
+    return m == 0.0f ? cf{0.0f, 0.0f} : r;
 }
 
 __device__ __forceinline__ float3 f3(float x, float y, float z) { return make_float3(x, y, z); }

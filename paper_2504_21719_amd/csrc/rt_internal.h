@@ -51,7 +51,8 @@ struct rt_scene {
     // 4-wide BVH collapsed from the binary one: 8 x float4 (128 B) per node,
     //   w0 = x_lo of children 0..3, w1 = x_hi, w2 = y_lo, w3 = y_hi,
     //   w4 = z_lo, w5 = z_hi, w6 = child refs (>= 0 wide node, < 0 leaf
-    //   slot ~r, RT_WIDE_EMPTY), w7 unused;
+    //   slot ~r, RT_WIDE_EMPTY), w7.x = leaf mask (int bits, bit c + 1 for
+    //   child c), the rest of w7 unused;
     // node 0 is the root.  Built when n_tri >= 2.  A ray reads, per axis, the
     // near plane first (lo for a positive direction component, else hi) and
     // the far one at the byte offset XOR 16.

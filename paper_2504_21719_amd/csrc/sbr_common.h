@@ -236,8 +236,9 @@ struct Ray {
     float sx, sy, sz;          // watertight shear constants
     int kx, ky, kz;            // watertight axis permutation
     unsigned nx, ny, nz;       // byte offsets of the near planes in a 4-wide node
-    float jx, jy, jz;          // reciprocal direction times kBoxSlack (far planes of box4)
-    float cnx, cny, cnz;       // -o i lowered past its rounding (near planes of box4)
+    float jx, jy, jz;          // reciprocal direction times kBoxSlack (far planes)
+    float cnx, cny, cnz;       // -o i rounded down (near planes of box4)
+    float cfx, cfy, cfz;       // -o j rounded up (far planes of box4)
 };
 
 __device__ __forceinline__ float pick(float a, float b, float c, int i) { return i == 0 ? a : (i == 1 ? b : c); }
@@ -248,6 +249,14 @@ __device__ __forceinline__ float pick(float a, float b, float c, int i) { return
 __device__ __forceinline__ float safe_inv(float d) {
     float a = fabsf(d) < 1e-20f ? copysignf(1e-20f, d) : d;
     return __builtin_amdgcn_rcpf(a);
+}
+
+// At most a b: the rounded product c lies within half an ulp of a b, and
+// |c| 2^-24 is between half an ulp and one, so c lowered by it and rounded is
+// c's lower neighbour (or c minus half an ulp of it at a power of two).
+__device__ __forceinline__ float mul_down(float a, float b) {
+    const float c = a * b;
+    return __builtin_fmaf(fabsf(c), -0x1p-24f, c);
 }
 
 __device__ __forceinline__ void ray_setup(Ray& r) {
@@ -273,29 +282,98 @@ __device__ __forceinline__ void ray_setup(Ray& r) {
     r.jx = r.ix * kBoxSlack;
     r.jy = r.iy * kBoxSlack;
     r.jz = r.iz * kBoxSlack;
-    // near planes are evaluated as p i + cn, one fma: cn is the rounded -o i
-    // lowered by 2^-22 |o i|, which exceeds the rounding of -o i and of the
-    // lowering itself (each at most 2^-24 |o i|), so p i + cn lies below
-    // (p - o) i and the fma's own rounding is relative, like the product's
-    // before, and covered by kBoxSlack: an entry distance can only come out
-    // smaller, never culling a box.  Far planes keep the difference and
-    // product, so boxes behind the origin (exit below tmin) stay culled as
-    // sharply as before.
-    {
-        const float cx = -r.ox * r.ix, cy = -r.oy * r.iy, cz = -r.oz * r.iz;
-        r.cnx = __builtin_fmaf(fabsf(cx), -0x1p-22f, cx);
-        r.cny = __builtin_fmaf(fabsf(cy), -0x1p-22f, cy);
-        r.cnz = __builtin_fmaf(fabsf(cz), -0x1p-22f, cz);
-    }
+    // planes are evaluated as one fma, p i + cn and p j + cf, with cn the
+    // product -o i rounded down and cf the product -o j rounded up (directed
+    // by its exact residual): p i + cn never exceeds (p - o) i and p j + cf
+    // never falls below (p - o) j, but for the fma's own rounding, which is
+    // relative and covered by kBoxSlack, so no box is culled that the exact
+    // test keeps.  The widening is at most one ulp of o i: lowering and
+    // raising by 2^-22 |o i| instead let a ray enter the boxes of the
+    // neighbours that its origin touches from behind.
+    r.cnx = mul_down(-r.ox, r.ix);
+    r.cny = mul_down(-r.oy, r.iy);
+    r.cnz = mul_down(-r.oz, r.iz);
+    r.cfx = -mul_down(r.ox, r.jx);
+    r.cfy = -mul_down(r.oy, r.jy);
+    r.cfz = -mul_down(r.oz, r.jz);
     r.nx = r.ix < 0.0f ? 16u : 0u;
     r.ny = r.iy < 0.0f ? 48u : 32u;
     r.nz = r.iz < 0.0f ? 80u : 64u;
 }
 
-// Watertight ray/triangle test.  Returns t (> t_min) or a negative value.
+__device__ __forceinline__ Ray make_ray(float3 o, float3 k) {
+    Ray r;
+    r.ox = o.x;
+    r.oy = o.y;
+    r.oz = o.z;
+    r.dx = k.x;
+    r.dy = k.y;
+    r.dz = k.z;
+    ray_setup(r);
+    return r;
+}
+
+// Makes a vector a new value to the optimiser (no instruction).
+__device__ __forceinline__ void hide(float3& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z)); }
+
+// Minima and maxima of numbers as single instructions (the library's quiet
+// signalling NaNs of their operands first, one instruction each).
+__device__ __forceinline__ float max_raw(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float min_raw(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max3_raw(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ float min3_raw(float a, float b, float c) {
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ __forceinline__ unsigned med3_u32(unsigned a, unsigned b, unsigned c) {
+    unsigned r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Watertight ray/triangle test: whether the ray hits at t > t_min.
 // Edge cases where a scaled barycentric is exactly zero are recomputed in
 // FP64, which is what makes shared edges watertight.
-__device__ __forceinline__ float tri_hit(const Ray& r, float4 a, float4 b, float4 c, float t_min) {
+// The part after the shear: returns whether the ray hits at t > t_min.
+// Straight-line but for the FP64 retry, which a wavefront enters only if one
+// of its lanes needs it: in a wavefront whose lanes test the same triangle an
+// early exit is seldom taken by all of them, and each costs a branch.
+__device__ __forceinline__ bool tri_sheared(float sz, float Ax, float Ay, float Ak, float Bx, float By, float Bk,
+                                            float Cx, float Cy, float Ck, float t_min, float& t) {
+#pragma clang fp contract(off)
+    float U = Cx * By - Cy * Bx;
+    float V = Ax * Cy - Ay * Cx;
+    float W = Bx * Ay - By * Ax;
+    const bool zero = (U == 0.0f) | (V == 0.0f) | (W == 0.0f);
+    if (__builtin_expect(__ballot(zero) != 0ull, 0)) {
+        if (zero) {
+            U = (float)((double)Cx * (double)By - (double)Cy * (double)Bx);
+            V = (float)((double)Ax * (double)Cy - (double)Ay * (double)Cx);
+            W = (float)((double)Bx * (double)Ay - (double)By * (double)Ax);
+        }
+    }
+    const bool out = (min3_raw(U, V, W) < 0.0f) & (max3_raw(U, V, W) > 0.0f);
+    const float det = U + V + W;
+    const float Az = sz * Ak, Bz = sz * Bk, Cz = sz * Ck;
+    const float T = U * Az + V * Bz + W * Cz;
+    t = T / det;
+    return (!out) & (det != 0.0f) & (t > t_min);
+}
+
+__device__ __forceinline__ bool tri_hit(const Ray& r, float4 a, float4 b, float4 c, float t_min, float& t) {
 #pragma clang fp contract(off)
     float Ax0 = a.x - r.ox, Ay0 = a.y - r.oy, Az0 = a.z - r.oz;
     float Bx0 = b.x - r.ox, By0 = b.y - r.oy, Bz0 = b.z - r.oz;
@@ -307,23 +385,79 @@ __device__ __forceinline__ float tri_hit(const Ray& r, float4 a, float4 b, float
     float By = pick(Bx0, By0, Bz0, r.ky) - r.sy * Bk;
     float Cx = pick(Cx0, Cy0, Cz0, r.kx) - r.sx * Ck;
     float Cy = pick(Cx0, Cy0, Cz0, r.ky) - r.sy * Ck;
-    float U = Cx * By - Cy * Bx;
-    float V = Ax * Cy - Ay * Cx;
-    float W = Bx * Ay - By * Ax;
-    if (U == 0.0f || V == 0.0f || W == 0.0f) {
-        U = (float)((double)Cx * (double)By - (double)Cy * (double)Bx);
-        V = (float)((double)Ax * (double)Cy - (double)Ay * (double)Cx);
-        W = (float)((double)Bx * (double)Ay - (double)By * (double)Ax);
-    }
-    if ((U < 0.0f || V < 0.0f || W < 0.0f) && (U > 0.0f || V > 0.0f || W > 0.0f)) return -1.0f;
-    float det = U + V + W;
-    if (det == 0.0f) return -1.0f;
-    float Az = r.sz * Ak, Bz = r.sz * Bk, Cz = r.sz * Ck;
-    float T = U * Az + V * Bz + W * Cz;
-    float t = T / det;
-    return t > t_min ? t : -1.0f;
+    return tri_sheared(r.sz, Ax, Ay, Ak, Bx, By, Bk, Cx, Cy, Ck, t_min, t);
 }
 
+// ---- wavefront-uniform loads through the scalar cache (the addresses, and so
+// the results, are the same on every active lane)
+// Value of the first active lane, in scalar registers.
+__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v) {
+    unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(v & 0xffffffffu));
+    unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+typedef float vf4 __attribute__((ext_vector_type(4)));
+typedef int vi4 __attribute__((ext_vector_type(4)));
+
+// Planes (near p, far q), child references and leaf mask of a 4-wide node.
+struct WideNode {
+    vf4 px, qx, py, qy, pz, qz;
+    vi4 rf;
+    unsigned leaf;       // bit c + 1 set: child c is a leaf
+};
+
+// All loads in one block with one wait: the compiler would split them (it
+// keeps address registers and results apart) and wait more than once.
+// `node` is below the number of nodes; nx, ny, nz are the near planes' offsets.
+__device__ __forceinline__ WideNode load_node_uniform(const float4* wide, int node, int nx, int ny, int nz) {
+    // below 2^32: the tree has fewer than 2^25 nodes
+    const uint64_t addr = (uint64_t)wide + (uint64_t)((unsigned)uniform(node) << 7);
+    WideNode w;
+    asm("s_load_dwordx4 %0, %8, %9\n\t"
+        "s_load_dwordx4 %1, %8, %10\n\t"
+        "s_load_dwordx4 %2, %8, %11\n\t"
+        "s_load_dwordx4 %3, %8, %12\n\t"
+        "s_load_dwordx4 %4, %8, %13\n\t"
+        "s_load_dwordx4 %5, %8, %14\n\t"
+        "s_load_dwordx4 %6, %8, 0x60\n\t"
+        "s_load_dword %7, %8, 0x70\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&s"(w.px), "=&s"(w.qx), "=&s"(w.py), "=&s"(w.qy), "=&s"(w.pz), "=&s"(w.qz), "=&s"(w.rf), "=&s"(w.leaf)
+        : "s"(addr), "s"(nx), "s"(nx ^ 16), "s"(ny), "s"(ny ^ 16), "s"(nz), "s"(nz ^ 16));
+    return w;
+}
+
+// tri_hit for triangle slot s, uniform across the wavefront, and rays that
+// share their axis permutation: the vertices are fetched component by
+// component in permuted order, so nothing is selected per lane; (ox, oy, oz)
+// is the permuted origin.  Bit for bit tri_hit.
+__device__ __forceinline__ bool tri_hit_axes(const Ray& r, const float4* tris, int s, int kx, int ky, int kz, float ox,
+                                             float oy, float oz, float t_min, float& t, int& id) {
+#pragma clang fp contract(off)
+    const uint64_t base = (uint64_t)tris + (uint64_t)(unsigned)uniform(s) * 48u;
+    float ax, ay, az, bx, by, bz, cx, cy, cz, idf;
+    asm("s_load_dword %0, %10, %11 offset:0x0\n\t"
+        "s_load_dword %1, %10, %12 offset:0x0\n\t"
+        "s_load_dword %2, %10, %13 offset:0x0\n\t"
+        "s_load_dword %3, %10, %11 offset:0x10\n\t"
+        "s_load_dword %4, %10, %12 offset:0x10\n\t"
+        "s_load_dword %5, %10, %13 offset:0x10\n\t"
+        "s_load_dword %6, %10, %11 offset:0x20\n\t"
+        "s_load_dword %7, %10, %12 offset:0x20\n\t"
+        "s_load_dword %8, %10, %13 offset:0x20\n\t"
+        "s_load_dword %9, %10, 0xc\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&s"(ax), "=&s"(ay), "=&s"(az), "=&s"(bx), "=&s"(by), "=&s"(bz), "=&s"(cx), "=&s"(cy), "=&s"(cz), "=&s"(idf)
+        : "s"(base), "s"(4 * kx), "s"(4 * ky), "s"(4 * kz));
+    id = __float_as_int(idf);
+    const float Ak = az - oz, Bk = bz - oz, Ck = cz - oz;
+    const float Ax = (ax - ox) - r.sx * Ak, Ay = (ay - oy) - r.sy * Ak;
+    const float Bx = (bx - ox) - r.sx * Bk, By = (by - oy) - r.sy * Bk;
+    const float Cx = (cx - ox) - r.sx * Ck, Cy = (cy - oy) - r.sy * Ck;
+    return tri_sheared(r.sz, Ax, Ay, Ak, Bx, By, Bk, Cx, Cy, Ck, t_min, t);
+}
 
 // Slab test of the two children of a node.  lo/hi layout as in rt_internal.h.
 __device__ __forceinline__ void box2(const Ray& r, float4 q0, float4 q1, float4 q2, float tmin, float tmax,
@@ -362,10 +496,9 @@ __device__ __forceinline__ float4 ld16(__amdgpu_buffer_rsrc_t rs, unsigned off) 
 // Slab test of the four children of the wide node at byte offset `base`.
 // Per axis the ray reads its near planes (lo for a positive direction
 // component, else hi) and its far planes, so that no min/max per axis is
-// needed: entry = max(near distances, tmin), exit = min(far distances) times
-// the slack.  Near distances take one fma each against the lowered offsets
-// of ray_setup; far distances a difference and a product.  Also returns the
-// four child references.
+// needed: entry = max(near distances, tmin), exit = min(far distances), the
+// slack folded into the far reciprocals; each distance is one fma against
+// the directed offsets of ray_setup.  Also returns the four child references.
 __device__ __forceinline__ void box4(const Ray& r, __amdgpu_buffer_rsrc_t rs, unsigned base, float tmin, float tmax,
                                      bool hit[4], float tent[4], int ref[4]) {
     const unsigned bx = base | r.nx, by = base | r.ny, bz = base | r.nz;
@@ -380,8 +513,9 @@ __device__ __forceinline__ void box4(const Ray& r, __amdgpu_buffer_rsrc_t rs, un
     for (int c = 0; c < 4; c++) {
         float a = fmaxf(fmaxf(__builtin_fmaf(nxa[c], r.ix, r.cnx), __builtin_fmaf(nya[c], r.iy, r.cny)),
                         fmaxf(__builtin_fmaf(nza[c], r.iz, r.cnz), tmin));
-        float b = fminf(fminf((fxa[c] - r.ox) * r.jx, (fya[c] - r.oy) * r.jy), (fza[c] - r.oz) * r.jz);
-        hit[c] = a <= fminf(b, tmax);
+        float b = fminf(fminf(__builtin_fmaf(fxa[c], r.jx, r.cfx), __builtin_fmaf(fya[c], r.jy, r.cfy)),
+                        fminf(__builtin_fmaf(fza[c], r.jz, r.cfz), tmax));
+        hit[c] = a <= b;
         tent[c] = a;
     }
     ref[0] = __float_as_int(rf.x);
@@ -552,11 +686,14 @@ __device__ __forceinline__ float3 diffuse_direction(float3 n, float cs, float ss
 __device__ __forceinline__ float3 te_direction(float3 k, float3 n) {
     float3 e = cross3(k, n);
     float l2 = dot3(e, e);
-    if (l2 < 1e-14f) {
-        float ax = fabsf(k.x), ay = fabsf(k.y), az = fabsf(k.z);
-        float3 a = (ax <= ay && ax <= az) ? f3(1, 0, 0) : (ay <= az ? f3(0, 1, 0) : f3(0, 0, 1));
-        e = cross3(k, a);
-        l2 = dot3(e, e);
+    const bool normal = l2 < 1e-14f;
+    if (__builtin_expect(__ballot(normal) != 0ull, 0)) {
+        if (normal) {
+            float ax = fabsf(k.x), ay = fabsf(k.y), az = fabsf(k.z);
+            float3 a = (ax <= ay && ax <= az) ? f3(1, 0, 0) : (ay <= az ? f3(0, 1, 0) : f3(0, 0, 1));
+            e = cross3(k, a);
+            l2 = dot3(e, e);
+        }
     }
     return e * __builtin_amdgcn_rsqf(l2);
 }
@@ -576,10 +713,9 @@ struct Bounce {
 __device__ __forceinline__ Bounce bounce_geometry(float3 k, float3 es, float3 nrm) {
     Bounce b;
     float kn = dot3(k, nrm);
-    if (kn > 0.0f) {          // orient the normal toward the incident side
-        nrm = nrm * -1.0f;
-        kn = -kn;
-    }
+    const float side = kn > 0.0f ? -1.0f : 1.0f;   // orient the normal toward the incident side
+    nrm = nrm * side;
+    kn = kn * side;
     b.c = fminf(1.0f, -kn);
     float3 ep = cross3(k, es);
     float3 eperp = te_direction(k, nrm);

@@ -6,22 +6,25 @@
 // differ.  The work indices are split into contiguous queues with separate
 // counters; a wavefront starts on its own queue and moves on to the next once
 // that is drained, until it has found every queue drained.  Per traced segment l the lane
-//   1. finds the closest hit through the LBVH (short LDS stack, spill to a
-//      per-lane global area sized from the tree depth), or by testing every
-//      triangle when accel = brute force (validation);
+//   1. finds the closest hit through the LBVH, the wavefront's lanes together
+//      while they want the same nodes, else each on its own (short LDS stack,
+//      spill to a per-lane global area sized from the tree depth), or by
+//      testing every triangle when accel = brute force (validation);
 //   2. deposits ||T C_T||^2 * lambda^2 / (4 pi N_S |M_i| |k_z|) into the plane
 //      cell it crosses, if any (estimator eq. radio-map-solver-ci-all-2-
 //      estimator for specular chains), either with one FP32 atomic or after
 //      summing same-cell crossings across the wavefront;
 //   3. unless the segment escaped or l = L, reflects specularly and updates
 //      the 2x2 field transfer matrix T (eq. fresnel_vac and the bases of
-//      eq. fresnel_in_vectors / eq. fresnel_out_vectors).
+//      eq. fresnel_in_vectors / eq. fresnel_out_vectors), or, where nothing
+//      needs T, the field T C_T itself.
 // The extended variant (template flag EXT) adds, per hit, the single-layer
 // slab coefficients, the sampled interaction type (specular or diffuse
 // reflection, transmission) with its 1/sqrt(q) weight, and early
 // termination by Russian roulette or gain thresholding before the next
 // segment; its random draws come from a counter-based Philox4x32-10 stream.
-// Ray state (origin, direction, basis, T) stays in VGPRs for the whole ray.
+// Ray state (origin, direction, basis, T or field) stays in VGPRs for the whole
+// ray.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -117,24 +120,36 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
     return lo;
 }
 
-__device__ __forceinline__ int lane_id() { return __lane_id(); }
+// A wavefront leaves the common walk once the visits that few lanes wanted add
+// up to this many of its active lanes (2, 4, 8 and 16 measure within 0.5 % of
+// each other on the city and the 1.02 M-triangle scene).
+constexpr int kPacketWaste = 8;
 
-// Value of lane 0 (the caller runs with every lane active), in scalar registers.
-__device__ __forceinline__ unsigned long long uniform_u64(unsigned long long v) {
-    unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(v & 0xffffffffu));
-    unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-    return ((unsigned long long)hi << 32) | lo;
+// Sum over the wavefront (every lane active), the same on every lane: rows of
+// 16 by shifts, then across the rows, all on the VALU's data-parallel
+// primitives (a butterfly through the LDS permute took six LDS round trips).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
 }
-
-__device__ __forceinline__ unsigned long long shfl_u64(unsigned long long v, int src) {
-    unsigned lo = __shfl((unsigned)(v & 0xffffffffu), src);
-    unsigned hi = __shfl((unsigned)(v >> 32), src);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
 __device__ __forceinline__ float wave_sum(float v) {
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    v = dpp_add<0x111, 0xf>(v);      // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);      // lane 15 of rows 0 and 2 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);      // lane 31 into rows 2 and 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// The kernel's argument block, with its address hidden from the optimiser:
+// each part of the ray loop reads the arguments it needs through the scalar
+// cache.  Without this the compiler loads all of them before the loop, runs
+// out of scalar registers and keeps over a hundred in vector-register lanes.
+__device__ __forceinline__ const FwdArgs& kernel_args() {
+    uintptr_t p = (uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const FwdArgs*)(const __attribute__((address_space(4))) FwdArgs*)p;
 }
 
 // Per-lane traversal stack: the first RT_STACK_LDS entries {node, entry
@@ -146,24 +161,41 @@ struct TravStack {
     int2* top;
     int stride;   // lanes per workgroup
     int sp;
+    unsigned gtid;
 };
 
-__device__ __forceinline__ void push_entry(const FwdArgs& a, TravStack& st, int64_t gtid, int ref, float key,
-                                           unsigned& overflow) {
+__device__ __forceinline__ int& spill_slot(const FwdArgs& a, int sp, unsigned gtid) {
+    return a.spill[(sp - RT_STACK_LDS) * a.spill_stride + gtid];
+}
+
+// Stores entry sp, beyond the LDS part, of a wavefront's stack; returns sp, or
+// sp - 1 if there is no room (cannot happen: the area is sized from the tree
+// depth).  Reads the arguments it needs: the callers seldom come here.
+__device__ __forceinline__ int push_spill(int ref, int sp, unsigned gtid, unsigned& overflow) {
+    const FwdArgs& a = kernel_args();
+    if (sp - RT_STACK_LDS >= a.spill_depth) {
+        overflow |= 1u;
+        return sp - 1;
+    }
+    spill_slot(a, sp, gtid) = ref;
+    return sp;
+}
+
+__device__ __forceinline__ void push_entry(const FwdArgs& a, TravStack& st, int ref, float key, unsigned& overflow) {
     if (st.sp < RT_STACK_LDS) {
         *st.top = make_int2(ref, __float_as_int(key));
         st.top += st.stride;
     } else if (st.sp - RT_STACK_LDS < a.spill_depth) {
-        a.spill[(st.sp - RT_STACK_LDS) * a.spill_stride + gtid] = ref;
+        spill_slot(a, st.sp, st.gtid) = ref;
     } else {
-        overflow++;   // cannot happen: the spill area is sized from the tree depth
+        overflow |= 1u;   // cannot happen: the spill area is sized from the tree depth
         return;
     }
     st.sp++;
 }
 
 // Pop until an entry whose box may still hold a hit closer than `lim`.
-__device__ __forceinline__ bool pop_entry(const FwdArgs& a, TravStack& st, int64_t gtid, float lim, int& node) {
+__device__ __forceinline__ bool pop_entry(const FwdArgs& a, TravStack& st, float lim, int& node) {
     while (st.sp > 0) {
         st.sp--;
         if (st.sp < RT_STACK_LDS) {
@@ -174,7 +206,156 @@ __device__ __forceinline__ bool pop_entry(const FwdArgs& a, TravStack& st, int64
                 return true;
             }
         } else {
-            node = a.spill[(st.sp - RT_STACK_LDS) * a.spill_stride + gtid];
+            node = spill_slot(a, st.sp, st.gtid);
+            return true;
+        }
+    }
+    return false;
+}
+
+// Best hit so far of one query: ties in t go to the smallest original id.
+struct Best {
+    float t, lim;     // distance; cull limit = t times the slack, kept finite (see closest_hit)
+    int id, slot;
+};
+
+__device__ __forceinline__ void take_hit(Best& b, bool hit, float t, int id, int s) {
+    const bool better = hit & ((t < b.t) | ((t == b.t) & (id < b.id)));
+    b.t = better ? t : b.t;
+    b.id = better ? id : b.id;
+    b.slot = better ? s : b.slot;
+    b.lim = better ? fminf(t * kBoxSlack, FLT_MAX) : b.lim;
+}
+
+// Value i (0..3, from its two lowest bits) of four.
+template <typename T>
+__device__ __forceinline__ T pick4(T v0, T v1, T v2, T v3, unsigned i) {
+    const T a = (i & 1u) ? v1 : v0, b = (i & 1u) ? v3 : v2;
+    return (i & 2u) ? b : a;
+}
+
+// First part of a 4-wide closest-hit query: the active lanes of the wavefront
+// walk the tree together, one node at a time, for as long as enough of them
+// want the same nodes.  Node planes and triangles are fetched once per
+// wavefront through the scalar cache, so a visit costs 11 VALU instructions
+// per child box and no vector memory access; a lane takes part with its own
+// cull limit.  Deferred children go to the same per-lane stack that the
+// per-lane loop uses (a lane that missed the child stores an INFINITY key, which
+// never passes a cull), so the wavefront can leave for the per-lane loop
+// after any node.  Returns false when the query is complete; else `node` is
+// the node at which this lane has to go on, or -1 if it has to pop one.
+//
+// Why: the launch order makes a wavefront's rays neighbours, and a plane
+// mirrors them together.  With 1e8 rays on the 1.02 M-triangle scene 61 of 64
+// lanes are active per segment, and a common walk takes 11.5 node visits and
+// 2.2 triangle tests per wavefront and segment where the per-lane loop takes
+// 14.3 and 4.6; its node visit issues about 118 VALU instructions and returns
+// 7 KiB through the vector memory path, both nearly saturated (93 % of the
+// VALU cycles).  The walk is bound by instruction issue and by branches: the
+// same walk with early exits in the triangle test and a branch per child and
+// push took 13.6 ms where this form takes 12.1 (15.2 without the walk); the
+// city, 1e7 rays, 0.88, 0.80 and 0.95 ms.
+template <bool REC>
+__device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int last, float tmin, Best& best,
+                                             int2* __restrict__ stk, int lstride, unsigned gtid, int& sp,
+                                             unsigned& n_nodes, unsigned& n_tris, unsigned& overflow, int& node_out) {
+    // the rays have to share the order of near and far planes and the axis
+    // permutation of the triangle test
+    const int nx = uniform((int)r.nx), ny = uniform((int)r.ny), nz = uniform((int)r.nz);
+    const int kx = uniform(r.kx), ky = uniform(r.ky), kz = uniform(r.kz);
+    const unsigned long long act = __ballot(true);
+    const int n_act = (int)__popcll(act);
+    node_out = 0;
+    if (__ballot((int)r.nx == nx && (int)r.ny == ny && (int)r.nz == nz && r.kx == kx && r.kz == kz) != act) return true;
+    const float ox = pick(r.ox, r.oy, r.oz, kx), oy = pick(r.ox, r.oy, r.oz, ky), oz = pick(r.ox, r.oy, r.oz, kz);
+    const float4* const wide = a.wide;
+    const float4* const tris = a.tris;
+    const int n_wide = a.n_wide;
+    int node = 0, waste = 0;
+    bool mine = true;                  // this lane wants `node`
+    for (int guard = 0; guard < n_wide; guard++) {
+        if (REC) n_nodes += mine ? 1u : 0u;
+        const WideNode w = load_node_uniform(wide, node, nx, ny, nz);
+        float te[4];
+        unsigned long long m[4];       // lanes that enter each child
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            te[c] = max3_raw(__builtin_fmaf(w.px[c], r.ix, r.cnx), __builtin_fmaf(w.py[c], r.iy, r.cny),
+                             max_raw(__builtin_fmaf(w.pz[c], r.iz, r.cnz), tmin));
+            const float f = min3_raw(__builtin_fmaf(w.qx[c], r.jx, r.cfx), __builtin_fmaf(w.qy[c], r.jy, r.cfy),
+                                     min_raw(__builtin_fmaf(w.qz[c], r.jz, r.cfz), best.lim));
+            m[c] = __ballot(te[c] <= f);
+        }
+        // bit c + 1: some lane enters child c
+        const unsigned hits = (m[0] ? 2u : 0u) | (m[1] ? 4u : 0u) | (m[2] ? 8u : 0u) | (m[3] ? 16u : 0u);
+        unsigned leaves = hits & w.leaf, inner = hits & ~w.leaf;
+        auto ref = [&](unsigned c) { return uniform(pick4(w.rf[0], w.rf[1], w.rf[2], w.rf[3], c)); };
+        // entry distance of child c, INFINITY on lanes that miss it
+        auto entry = [&](unsigned c) {
+            const float e = pick4(te[0], te[1], te[2], te[3], c);
+            return __builtin_amdgcn_inverse_ballot_w64(pick4(m[0], m[1], m[2], m[3], c)) ? e : INFINITY;
+        };
+        while (leaves) {
+            const unsigned c = (unsigned)__builtin_ctz(leaves) - 1u;
+            leaves &= leaves - 1u;
+            const int s = ~ref(c);
+            const bool want = (entry(c) <= best.lim) & (s != last);
+            if (REC) n_tris += want ? 1u : 0u;
+            float t;
+            int id;
+            const bool hit = tri_hit_axes(r, tris, s, kx, ky, kz, ox, oy, oz, tmin, t, id);
+            take_hit(best, want & hit, t, id, s);
+        }
+        // internal children: the one that most lanes enter first is descended,
+        // the others are deferred
+        int next = -1;
+        float key = INFINITY;
+        if (inner) {
+            unsigned c = (unsigned)__builtin_ctz(inner) - 1u;
+            next = ref(c);
+            key = entry(c);
+            inner &= inner - 1u;
+            while (inner) {
+                c = (unsigned)__builtin_ctz(inner) - 1u;
+                inner &= inner - 1u;
+                const int r2 = ref(c);
+                const float k2 = entry(c);
+                const bool swap = (int)__popcll(__ballot(k2 < key)) > (int)__popcll(__ballot(key < k2));
+                const int far_ref = swap ? next : r2;
+                if (__builtin_expect(sp < RT_STACK_LDS, 1))
+                    stk[sp * lstride] = make_int2(far_ref, __float_as_int(swap ? key : k2));
+                else
+                    sp = push_spill(far_ref, sp, gtid, overflow);
+                sp++;
+                next = swap ? r2 : next;
+                key = swap ? k2 : key;
+            }
+        }
+        mine = key <= best.lim;
+        unsigned long long live = __ballot(mine);
+        while (live == 0ull) {
+            if (sp == 0) return false;
+            sp--;
+            if (__builtin_expect(sp < RT_STACK_LDS, 1)) {
+                const int2 e = stk[sp * lstride];
+                next = uniform(e.x);
+                mine = __int_as_float(e.y) <= best.lim;
+            } else {
+                next = uniform(spill_slot(kernel_args(), sp, gtid));
+                mine = true;
+            }
+            live = __ballot(mine);
+        }
+        node = next;
+        if (__builtin_expect((unsigned)node >= (unsigned)n_wide, 0)) {
+            overflow |= 1u;
+            return false;
+        }
+        // a visit that fewer than a third of the lanes want costs more than
+        // its share of the per-lane loop: leave after a few of them
+        waste = max(0, waste + n_act - 3 * (int)__popcll(live));
+        if (__builtin_expect(waste > kPacketWaste * n_act, 0)) {
+            node_out = mine ? node : -1;
             return true;
         }
     }
@@ -182,114 +363,123 @@ __device__ __forceinline__ bool pop_entry(const FwdArgs& a, TravStack& st, int64
 }
 
 // Closest hit of ray r among all triangles but `last` (a slot).  Ties in t go
-// to the smallest original triangle id.  Returns the slot or -1.
-template <bool BRUTE, bool WIDE>
-__device__ __forceinline__ int closest_hit(const FwdArgs& a, const Ray& r, int last, float& t_best, int& id_best,
-                                           int2* __restrict__ stk, int lstride, int64_t gtid,
-                                           unsigned& n_nodes, unsigned& n_tris, unsigned& overflow) {
-    t_best = INFINITY;
-    id_best = 0x7fffffff;
-    int slot_best = -1;
-    // cull limit: t_best times the slack, kept finite so that the INFINITY
-    // keys of missed, leaf and empty slots never pass it, also before the
-    // first hit; updated with t_best
-    float lim = FLT_MAX;
+// to the smallest original triangle id.  best.slot = -1: none.
+template <bool BRUTE, bool WIDE, bool REC>
+__device__ __forceinline__ Best closest_hit(const FwdArgs& a, float3 o, float3 k, int last, int2* __restrict__ stk,
+                                            int lstride, unsigned gtid, unsigned& n_nodes, unsigned& n_tris,
+                                            unsigned& overflow) {
+    // cull limit: t times the slack, kept finite so that the INFINITY keys of
+    // missed, leaf and empty slots never pass it, also before the first hit;
+    // updated with t
+    Best best = {INFINITY, FLT_MAX, 0x7fffffff, -1};
     // canonical once, so that the min/max below need no per-use quieting
     const float tmin = __builtin_canonicalizef(a.t_min);
-    if (a.n_tri == 0) return -1;
+    if (a.n_tri == 0) return best;
+    Ray r = make_ray(o, k);
     auto test = [&](int s) {
         if (s == last) return;
         float4 v0 = a.tris[3 * (int64_t)s], v1 = a.tris[3 * (int64_t)s + 1], v2 = a.tris[3 * (int64_t)s + 2];
-        n_tris++;
-        float t = tri_hit(r, v0, v1, v2, tmin);
-        if (t > 0.0f) {
-            int id = __float_as_int(v0.w);
-            if (t < t_best || (t == t_best && id < id_best)) {
-                t_best = t;
-                id_best = id;
-                slot_best = s;
-                lim = fminf(t * kBoxSlack, FLT_MAX);
-            }
-        }
+        if (REC) n_tris++;
+        float t;
+        const bool hit = tri_hit(r, v0, v1, v2, tmin, t);
+        take_hit(best, hit, t, __float_as_int(v0.w), s);
     };
     if (BRUTE) {
         for (int s = 0; s < a.n_tri; s++) test(s);
-        return slot_best;
+        return best;
     }
     if (a.root < 0) {
         test(~a.root);
-        return slot_best;
+        return best;
     }
-    TravStack st{stk, lstride, 0};
+    TravStack st{stk, lstride, 0, gtid};
     if (WIDE) {
         // 4-wide traversal: four slab tests per node fetch (empty child slots
         // hold inverted boxes and never hit); leaf children are tested at once,
         // internal hits are sorted by entry distance, the nearest is descended
         // and the others are pushed farthest first
         int node = 0;
+        int sp = 0;
+        if (!packet_phase<REC>(a, r, last, tmin, best, stk, lstride, gtid, sp, n_nodes, n_tris, overflow, node)) return best;
+        st.sp = sp;
+        st.top = stk + min(sp, RT_STACK_LDS) * lstride;
+        if (node < 0 && !pop_entry(a, st, best.lim, node)) return best;
+        // the ray's constants are made again (from hidden copies, so that they
+        // are not the same values to the compiler): held across the loop above
+        // they would cost its registers
+        hide(o);
+        hide(k);
+        r = make_ray(o, k);
         const __amdgpu_buffer_rsrc_t rs = wide_rsrc(a.wide, a.n_wide);
         for (int guard = 0; guard < a.n_tri; guard++) {
-            n_nodes++;
+            if (REC) n_nodes++;
             bool h[4];
             float te[4];
             int ref[4];
-            box4(r, rs, (unsigned)node << 7, tmin, lim, h, te, ref);
-            float key[4];
+            box4(r, rs, (unsigned)node << 7, tmin, best.lim, h, te, ref);
+            // keys of the internal hits: the entry distance's bits with the
+            // child's index in the lowest two (distances are >= 0, so the bits
+            // order like the numbers, and clearing two of them only brings a
+            // child nearer); the others sort last and, as NaN, pass no cull
+            unsigned key[4];
             unsigned leaves = 0;
 #pragma unroll
             for (int c = 0; c < 4; c++) {
-                key[c] = (h[c] && ref[c] >= 0) ? te[c] : INFINITY;
+                key[c] = (h[c] && ref[c] >= 0) ? (__float_as_uint(te[c]) & ~3u) | (unsigned)c : 0xffffffffu;
                 leaves |= (h[c] && ref[c] < 0) ? 1u << c : 0u;
             }
+            // select by the bits of c (selects, not a branch per slot)
+            auto child = [&](unsigned c) {
+                return pick4(ref[0], ref[1], ref[2], ref[3], c);
+            };
             // one triangle-test body for the whole wavefront: it runs as many
             // times as the lane with the most leaf hits needs
             while (leaves) {
-                const int c = __builtin_ctz(leaves);
+                const unsigned c = (unsigned)__builtin_ctz(leaves);
                 leaves &= leaves - 1u;
-                // select by the bits of c (selects, not a branch per slot)
-                const int r01 = (c & 1) ? ref[1] : ref[0];
-                const int r23 = (c & 1) ? ref[3] : ref[2];
-                test(~((c & 2) ? r23 : r01));
+                test(~child(c));
             }
-            // sort the four (key, ref) pairs by key (misses sort last)
-#define RT_CSWAP(i, j)                                  \
-    if (key[j] < key[i]) {                              \
-        float tk = key[i];                              \
-        key[i] = key[j];                                \
-        key[j] = tk;                                    \
-        int tr = ref[i];                                \
-        ref[i] = ref[j];                                \
-        ref[j] = tr;                                    \
-    }
-            RT_CSWAP(0, 1) RT_CSWAP(2, 3) RT_CSWAP(0, 2) RT_CSWAP(1, 3) RT_CSWAP(1, 2)
-#undef RT_CSWAP
+            // sorted: the least, middle and largest of the first three, then the
+            // fourth between them
+            const unsigned lo = min(min(key[0], key[1]), key[2]), hi = max(max(key[0], key[1]), key[2]);
+            const unsigned mid = med3_u32(key[0], key[1], key[2]);
+            const unsigned srt[4] = {min(lo, key[3]), med3_u32(lo, mid, key[3]), med3_u32(mid, hi, key[3]), max(hi, key[3])};
             // children entered beyond the closest hit so far are dropped (the
             // same outcome as a box test with the new bound)
-            if (key[0] <= lim) {
-#pragma unroll
-                for (int c = 3; c >= 1; c--)
-                    if (key[c] <= lim) push_entry(a, st, gtid, ref[c], key[c], overflow);
-                node = ref[0];
-            } else if (!pop_entry(a, st, gtid, lim, node)) {
+            if (__uint_as_float(srt[0]) <= best.lim) {
+                // seldom more than one child in any lane: one test then skips all
+                // the pushes
+                if (__ballot(__uint_as_float(srt[1]) <= best.lim)) {
+                    if (__ballot(__uint_as_float(srt[2]) <= best.lim)) {
+                        if (__uint_as_float(srt[3]) <= best.lim)
+                            push_entry(a, st, child(srt[3]), __uint_as_float(srt[3]), overflow);
+                        if (__uint_as_float(srt[2]) <= best.lim)
+                            push_entry(a, st, child(srt[2]), __uint_as_float(srt[2]), overflow);
+                    }
+                    if (__uint_as_float(srt[1]) <= best.lim)
+                        push_entry(a, st, child(srt[1]), __uint_as_float(srt[1]), overflow);
+                }
+                node = child(srt[0]);
+            } else if (!pop_entry(a, st, best.lim, node)) {
                 break;
             }
         }
-        return slot_best;
+        return best;
     }
     int node = a.root;
     // every internal node is visited at most once per query; the bound only
     // guards against a malformed tree
     for (int guard = 0; guard < a.n_tri; guard++) {
         if ((unsigned)node >= (unsigned)(a.n_tri - 1)) {
-            overflow++;
+            overflow |= 1u;
             break;
         }
-        n_nodes++;
+        if (REC) n_nodes++;
         const float4* q = a.nodes + 4 * (int64_t)node;
         float4 q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
         bool hL, hR;
         float tL, tR;
-        box2(r, q0, q1, q2, tmin, t_best * kBoxSlack, hL, hR, tL, tR);
+        box2(r, q0, q1, q2, tmin, best.t * kBoxSlack, hL, hR, tL, tR);
         int cl = __float_as_int(q3.x), cr = __float_as_int(q3.y);
         if (hL && cl < 0) {
             test(~cl);
@@ -303,67 +493,135 @@ __device__ __forceinline__ int closest_hit(const FwdArgs& a, const Ray& r, int l
             // the far child's entry distance goes with it, so that it can be
             // dropped at pop time without fetching its node
             const bool lnear = tL <= tR;
-            push_entry(a, st, gtid, lnear ? cr : cl, lnear ? tR : tL, overflow);
+            push_entry(a, st, lnear ? cr : cl, lnear ? tR : tL, overflow);
             node = lnear ? cl : cr;
         } else if (hL) {
             node = cl;
         } else if (hR) {
             node = cr;
-        } else if (!pop_entry(a, st, gtid, t_best * kBoxSlack, node)) {
+        } else if (!pop_entry(a, st, best.t * kBoxSlack, node)) {
             break;
         }
     }
-    return slot_best;
+    return best;
 }
 
-template <bool BRUTE, int MODE, bool WIDE, bool EXT>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k_forward(const FwdArgs a) {
+// What a ray carries from segment to segment (template parameter FIELD):
+//   0          the 2x2 transfer matrix T and the launch patterns C (E = T C),
+//              which the tape stores and the extensions' decisions are made of;
+//   1, 2       the fields E of one or two polarisations: half the registers and
+//              arithmetic of T with one polarisation.
+template <int FIELD>
+struct FieldState {
+    cf e[FIELD][2];
+    __device__ __forceinline__ void set(int p, float ct, float cp) {
+        e[p][0] = cf{ct, 0.0f};
+        e[p][1] = cf{cp, 0.0f};
+    }
+    __device__ __forceinline__ void launch() {}
+    __device__ __forceinline__ float power(int p) const { return cabs2(e[p][0]) + cabs2(e[p][1]); }
+    // E <- diag(c_perp, -c_par) W E
+    __device__ __forceinline__ void interact(const Bounce& b, cf cperp, cf cpar) {
+        const cf mr = cf{-cpar.re, -cpar.im};
+#pragma unroll
+        for (int p = 0; p < FIELD; p++) {
+            const cf u0 = cadd(cscale(e[p][0], b.w00), cscale(e[p][1], b.w01));
+            const cf u1 = cadd(cscale(e[p][0], b.w10), cscale(e[p][1], b.w11));
+            e[p][0] = cmul(cperp, u0);
+            e[p][1] = cmul(mr, u1);
+        }
+    }
+};
+
+template <>
+struct FieldState<0> {
+    cf Ta, Tb, Tc, Td;
+    float c0t, c0p, c1t, c1p;   // C_T per polarisation
+    __device__ __forceinline__ void set(int p, float ct, float cp) {
+        if (p == 0) {
+            c0t = ct;
+            c0p = cp;
+        } else {
+            c1t = ct;
+            c1p = cp;
+        }
+    }
+    __device__ __forceinline__ void launch() {
+        Ta = cf{1, 0};
+        Tb = cf{0, 0};
+        Tc = cf{0, 0};
+        Td = cf{1, 0};
+    }
+    __device__ __forceinline__ float power(int p) const {
+        const float ct = p == 0 ? c0t : c1t, cp = p == 0 ? c0p : c1p;
+        const cf e0 = cadd(cscale(Ta, ct), cscale(Tb, cp));
+        const cf e1 = cadd(cscale(Tc, ct), cscale(Td, cp));
+        return cabs2(e0) + cabs2(e1);
+    }
+    // T <- diag(c_perp, -c_par) W T: the new basis is (e_perp, k' x e_perp),
+    // whose second vector is -e_par of the outgoing wave for both k' = k_r and
+    // k' = k
+    __device__ __forceinline__ void interact(const Bounce& b, cf cperp, cf cpar) {
+        cf na = cadd(cscale(Ta, b.w00), cscale(Tc, b.w01));
+        cf nb = cadd(cscale(Tb, b.w00), cscale(Td, b.w01));
+        cf nc = cadd(cscale(Ta, b.w10), cscale(Tc, b.w11));
+        cf nd = cadd(cscale(Tb, b.w10), cscale(Td, b.w11));
+        Ta = cmul(cperp, na);
+        Tb = cmul(cperp, nb);
+        cf mr = cf{-cpar.re, -cpar.im};
+        Tc = cmul(mr, nc);
+        Td = cmul(mr, nd);
+    }
+};
+
+// REC: the call has records, statistics or a tape; FIELD: see FieldState (0
+// with REC and EXT).
+template <bool BRUTE, int MODE, bool WIDE, bool EXT, bool REC, int FIELD>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k_forward(const FwdArgs) {
     extern __shared__ int2 s_stack[];
     const int lstride = blockDim.x;
     int2* stk = s_stack + threadIdx.x;
-    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = lane_id();
-    const unsigned long long lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int L = a.L;
-    const int stride = L + 1;
-    const int W = a.pl.W, H = a.pl.H;
+    const unsigned gtid = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = (int)__lane_id();
+    constexpr bool FIELDS = MODE != MODE_GEOM;
+    constexpr bool TAPE = REC || MODE == MODE_GEOM;
 
     unsigned st_seg = 0, st_cross = 0, st_nodes = 0, st_tris = 0, st_over = 0;
 
     bool active = false;
     bool exhausted = false;
     // this wavefront's first queue (held in scalar registers)
-    int q = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % a.nq));
+    int q = uniform((int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % (unsigned)kernel_args().nq));
     int drained = 0;                   // queues found drained so far
-    const unsigned long long claim = (unsigned long long)a.claim;   // work indices per atomic
     unsigned long long res_b = 0, res_e = 0;                         // claimed, not yet started
     int64_t rid = 0;          // ray index relative to ray_begin
     int l = 0;
     int last = -1;
     float3 o = f3(0, 0, 0), k = f3(0, 0, 0), es = f3(0, 0, 0);
-    cf Ta = {1, 0}, Tb = {0, 0}, Tc = {0, 0}, Td = {1, 0};
-    float c0t = 0.f, c0p = 0.f, c1t = 0.f, c1p = 0.f;   // C_T per polarisation
-    float kap = a.tx.kappa;   // lambda^2 / (4 pi N_S |M|) of the lane's transmitter
+    FieldState<FIELDS ? FIELD : 0> fs;
+    float kap = 0.0f;         // lambda^2 / (4 pi N_S |M|) of the lane's transmitter, times |alpha|^2
     float rlen = 0.0f;        // unfolded length to the last interaction (early termination only)
-    float* mapb = a.map;      // map of the lane's transmitter
-    // several transmitters: lattice index of the lane's ray within its
-    // transmitter (the counter of its random streams, as in a single call)
-    // and 1 / kappa of that transmitter
+    // several transmitters: the map of the lane's transmitter, the lattice
+    // index of its ray there (the counter of its random streams, as in a
+    // single call), 1 / kappa and the output slot of that transmitter
+    float* mapb = nullptr;
     int64_t nlat = 0;
-    float ikap = a.inv_kappa;
-    int tslot = 0;            // output slot of the lane's transmitter (several transmitters)
+    float ikap = 0.0f;
+    int tslot = 0;
 
     while (true) {
         // ---- refill lanes without a ray: from this wavefront's reservoir of
         // claimed work indices, claiming a new batch from the queues when the
         // reservoir cannot cover every idle lane
         if (!exhausted || res_b < res_e) {
+            const FwdArgs& a = kernel_args();
             unsigned long long need = __ballot(!active);
             if (need && (__popcll(need) >= a.refill || need == ~0ull)) {
                 const unsigned cnt = (unsigned)__popcll(need);
                 // wave-uniform: every value below is the same on all lanes
                 unsigned long long b1 = res_b, e1 = res_e, b2 = 0, e2 = 0;
                 if (e1 - b1 < cnt && !exhausted) {
+                    const unsigned long long claim = (unsigned long long)a.claim;   // work indices per atomic
                     while (true) {
                         // queue q holds work indices [qb, qe): per or per + 1 of them
                         const unsigned long long qb = (unsigned long long)q * a.qper + (unsigned)min(q, a.qrem);
@@ -400,13 +658,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                 res_b = take1 < n1 ? b1 + take1 : b2 + take2;
                 res_e = take1 < n1 ? e1 : e2;
                 if (!active) {
-                    const unsigned long long rank = (unsigned long long)__popcll(need & lt);
-                    const bool mine = rank < take1 + take2;
-                    const unsigned long long my = rank < take1 ? b1 + rank : b2 + (rank - take1);
+                    const unsigned rank = __builtin_amdgcn_mbcnt_hi((unsigned)(need >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)need, 0u));
+                    const bool mine = rank < (unsigned)(take1 + take2);
+                    const unsigned long long my = rank < (unsigned)take1 ? b1 + rank : b2 + (rank - (unsigned)take1);
                     if (mine) {
                         rid = (int64_t)my;
                         int64_t n;
-                        TxDesc td;
+                        const TxDesc* tp;
                         const int64_t M = (int64_t)1 << a.olog2m;
                         if (MODE == MODE_SINGLE) {
                             n = a.ray_begin + rid;
@@ -417,29 +676,34 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                                     n = c0 + a.operm[((n - c0) + a.oshift[c]) & (M - 1)];
                             }
                             rid = n - a.ray_begin;   // records stay indexed by lattice index
-                            td = a.tx;
+                            tp = &a.tx;
                         } else {
                             int t = find_tx(a.prefix, a.n_tx, rid);
                             n = rid - a.prefix[t];
-                            td = a.txs[t];
-                            if (a.operm && (n >> a.olog2m) < td.n_chunks) {
+                            tp = a.txs + t;
+                            if (a.operm && (n >> a.olog2m) < tp->n_chunks) {
                                 int64_t c = n >> a.olog2m, c0 = c << a.olog2m;
-                                n = c0 + a.operm[((n - c0) + a.oshift[td.shift0 + c]) & (M - 1)];
+                                n = c0 + a.operm[((n - c0) + a.oshift[tp->shift0 + c]) & (M - 1)];
                                 // the geometry tape stays in launch order (a
                                 // wavefront of the field pass then reads
                                 // consecutive records of nearby directions)
                                 if (MODE != MODE_GEOM) rid = a.prefix[t] + n;
                             }
-                            kap = td.kappa;
                             mapb = a.map + (int64_t)a.slots[t] * a.slot_stride;
                             nlat = n;
-                            ikap = 1.0f / td.kappa;
+                            ikap = 1.0f / tp->kappa;
                             tslot = a.slots[t];
                         }
+                        const TxDesc& td = *tp;
                         Launch Lr = fib_launch(n, td.n_rays);
-                        if (MODE != MODE_GEOM) {
-                            tx_pattern<float>(Lr, td, td.pol == 1 ? 1 : 0, c0t, c0p);
-                            if (a.npol == 2) tx_pattern<float>(Lr, td, 1, c1t, c1p);
+                        if (FIELDS) {
+                            float ct, cp;
+                            tx_pattern<float>(Lr, td, td.pol == 1 ? 1 : 0, ct, cp);
+                            fs.set(0, ct, cp);
+                            if (FIELD == 2 || (FIELD == 0 && a.npol == 2)) {
+                                tx_pattern<float>(Lr, td, 1, ct, cp);
+                                fs.set(1, ct, cp);
+                            }
                             // a transmit array scales the ray's field by alpha
                             // and its weights by |alpha|^2
                             kap = td.kappa;
@@ -448,22 +712,22 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                         k = f3((float)Lr.kx, (float)Lr.ky, (float)Lr.kz);
                         es = f3((float)Lr.tx, (float)Lr.ty, (float)Lr.tz);
                         o = f3(td.pos[0], td.pos[1], td.pos[2]);
-                        Ta = cf{1, 0};
-                        Tb = cf{0, 0};
-                        Tc = cf{0, 0};
-                        Td = cf{1, 0};
+                        fs.launch();
                         l = 0;
                         rlen = 0.0f;
                         last = -1;
                         active = true;
-                        if (a.hits) {
-                            for (int j = 0; j < stride; j++) a.hits[rid * stride + j] = -2;
-                        }
-                        if (a.cells) {
-                            for (int j = 0; j < stride; j++) a.cells[rid * stride + j] = -1;
-                        }
-                        if (a.weights) {
-                            for (int j = 0; j < stride; j++) a.weights[rid * stride + j] = 0.0f;
+                        if (REC) {
+                            const int stride = a.L + 1;
+                            if (a.hits) {
+                                for (int j = 0; j < stride; j++) a.hits[rid * stride + j] = -2;
+                            }
+                            if (a.cells) {
+                                for (int j = 0; j < stride; j++) a.cells[rid * stride + j] = -1;
+                            }
+                            if (a.weights) {
+                                for (int j = 0; j < stride; j++) a.weights[rid * stride + j] = 0.0f;
+                            }
                         }
                     }
                 }
@@ -472,110 +736,99 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
         if (__ballot(active) == 0ull) break;
 
         // ---- closest hit of the current segment
-        int slot = -1, hit_id = -1, cell = -1;
+        int slot = -1, cell = -1;
         float t_hit = INFINITY;
         float w0 = 0.f, w1 = 0.f;
         if (active) {
-            Ray r;
-            r.ox = o.x;
-            r.oy = o.y;
-            r.oz = o.z;
-            r.dx = k.x;
-            r.dy = k.y;
-            r.dz = k.z;
-            ray_setup(r);
-            int idb;
-            slot = closest_hit<BRUTE, WIDE>(a, r, last, t_hit, idb, stk, lstride, gtid, st_nodes,
-                                            st_tris, st_over);
-            hit_id = slot >= 0 ? idb : -1;
-            st_seg++;
+            const Best best = closest_hit<BRUTE, WIDE, REC>(kernel_args(), o, k, last, stk, lstride, gtid, st_nodes,
+                                                            st_tris, st_over);
+            slot = best.slot;
+            t_hit = best.t;
+            if (REC) st_seg++;
+            const FwdArgs& a = kernel_args();
+            const int W = a.pl.W, H = a.pl.H;
             // ---- plane crossing of this segment
-            if (k.z != 0.0f) {
-                float tm = (a.pl.z - o.z) * __builtin_amdgcn_rcpf(k.z);
-                if (tm > 0.0f && tm < t_hit) {
-                    float x = o.x + tm * k.x, y = o.y + tm * k.y;
-                    float fx = (x - a.pl.x0) * a.pl.inv_dx, fy = (y - a.pl.y0) * a.pl.inv_dy;
-                    if (fx >= 0.0f && fy >= 0.0f && fx < (float)W && fy < (float)H) {
-                        int i = min((int)fx, W - 1), j = min((int)fy, H - 1);
-                        cell = j * W + i;
-                        st_cross++;
-                    }
-                }
-                if (MODE != MODE_GEOM && cell >= 0) {
-                        float g = kap * __builtin_amdgcn_rcpf(fabsf(k.z));
-                        cf e0 = cadd(cscale(Ta, c0t), cscale(Tb, c0p));
-                        cf e1 = cadd(cscale(Tc, c0t), cscale(Td, c0p));
-                        w0 = g * (cabs2(e0) + cabs2(e1));
-                        if (a.npol == 2) {
-                            cf f0 = cadd(cscale(Ta, c1t), cscale(Tb, c1p));
-                            cf f1 = cadd(cscale(Tc, c1t), cscale(Td, c1p));
-                            w1 = g * (cabs2(f0) + cabs2(f1));
-                        }
+            {
+                const float tm = (a.pl.z - o.z) * __builtin_amdgcn_rcpf(k.z);
+                const float x = o.x + tm * k.x, y = o.y + tm * k.y;
+                const float fx = (x - a.pl.x0) * a.pl.inv_dx, fy = (y - a.pl.y0) * a.pl.inv_dy;
+                const bool cross = (k.z != 0.0f) & (tm > 0.0f) & (tm < t_hit) & (fx >= 0.0f) & (fy >= 0.0f) &
+                                   (fx < (float)W) & (fy < (float)H);
+                cell = cross ? min((int)fy, H - 1) * W + min((int)fx, W - 1) : -1;
+                if (REC) st_cross += cross ? 1u : 0u;
+                if (FIELDS && cross) {
+                    float g = kap * __builtin_amdgcn_rcpf(fabsf(k.z));
+                    w0 = g * fs.power(0);
+                    if (FIELD == 2 || (FIELD == 0 && a.npol == 2)) w1 = g * fs.power(1);
                 }
             }
-            if (a.hits) a.hits[rid * stride + l] = hit_id;
-            if (a.cells) a.cells[rid * stride + l] = cell;
-            if (a.weights) a.weights[rid * stride + l] = w0;
-            if (a.tape_seg) {
+            if (REC) {
+                const int stride = a.L + 1;
+                if (a.hits) a.hits[rid * stride + l] = slot >= 0 ? best.id : -1;
+                if (a.cells) a.cells[rid * stride + l] = cell;
+                if (a.weights) a.weights[rid * stride + l] = w0;
+            }
+            if (TAPE && a.tape_seg) {
                 const int64_t tn = a.tape_n;
                 float4* ts = a.tape_seg + (int64_t)l * a.tape_groups * tn + rid;
                 ts[0] = make_float4(k.x, k.y, k.z, __int_as_float(slot));
                 ts[tn] = make_float4(es.x, es.y, es.z, __int_as_float(cell));
-                if (MODE != MODE_GEOM) {
-                    ts[2 * tn] = make_float4(Ta.re, Ta.im, Tb.re, Tb.im);
-                    ts[3 * tn] = make_float4(Tc.re, Tc.im, Td.re, Td.im);
+                if constexpr (FIELDS && FIELD == 0) {
+                    ts[2 * tn] = make_float4(fs.Ta.re, fs.Ta.im, fs.Tb.re, fs.Tb.im);
+                    ts[3 * tn] = make_float4(fs.Tc.re, fs.Tc.im, fs.Td.re, fs.Td.im);
                 }
             }
         }
 
         // ---- deposit (all lanes reconverged here)
-        if (MODE == MODE_GEOM) {
-            // fields are computed later, per material sample
-        } else if (a.deposit == 2) {
-            // at most kDepositGroups same-cell groups are summed across the
-            // wavefront; lanes left over add their own crossings (crossings
-            // scattered over many cells would otherwise cost one wavefront
-            // reduction per cell)
-            unsigned long long pend = __ballot(cell >= 0);
-            bool done = cell < 0;
-            int groups = 0;
-            while (pend) {
-                if (groups == kDepositGroups) {
-                    if (!done) {
-                        unsafeAtomicAdd(mapb + cell, w0);
-                        if (a.npol == 2) unsafeAtomicAdd(mapb + a.map_stride + cell, w1);
+        if (FIELDS) {
+            const FwdArgs& a = kernel_args();
+            const bool two = FIELD == 2 || (FIELD == 0 && a.npol == 2);
+            float* const map = MODE == MODE_SINGLE ? a.map : mapb;
+            if (a.deposit == 2) {
+                // at most kDepositGroups same-cell groups are summed across the
+                // wavefront; lanes left over add their own crossings (crossings
+                // scattered over many cells would otherwise cost one wavefront
+                // reduction per cell)
+                unsigned long long pend = __ballot(cell >= 0);
+                bool done = cell < 0;
+                int groups = 0;
+                while (pend) {
+                    if (groups == kDepositGroups) {
+                        if (!done) {
+                            unsafeAtomicAdd(map + cell, w0);
+                            if (two) unsafeAtomicAdd(map + a.map_stride + cell, w1);
+                        }
+                        break;
                     }
-                    break;
-                }
-                groups++;
-                int leader = __ffsll((long long)pend) - 1;
-                int lc = __shfl(cell, leader);
-                bool mine = !done && cell == lc;
-                if (MODE == MODE_MULTI) {
+                    groups++;
+                    const int leader = __builtin_ctzll(pend);
+                    const int lc = __builtin_amdgcn_readlane(cell, leader);
+                    bool mine = !done && cell == lc;
                     // lanes of other transmitters deposit into other maps
-                    const int ls = __shfl(tslot, leader);
-                    mine = mine && tslot == ls;
+                    if (MODE == MODE_MULTI) mine = mine && tslot == __builtin_amdgcn_readlane(tslot, leader);
+                    unsigned long long grp = __ballot(mine);
+                    float v0 = wave_sum(mine ? w0 : 0.0f);
+                    float v1 = 0.0f;
+                    if (two) v1 = wave_sum(mine ? w1 : 0.0f);
+                    if (lane == leader) {
+                        unsafeAtomicAdd(map + lc, v0);
+                        if (two) unsafeAtomicAdd(map + a.map_stride + lc, v1);
+                    }
+                    if (mine) done = true;
+                    pend &= ~grp;
                 }
-                unsigned long long grp = __ballot(mine);
-                float v0 = wave_sum(mine ? w0 : 0.0f);
-                float v1 = 0.0f;
-                if (a.npol == 2) v1 = wave_sum(mine ? w1 : 0.0f);
-                if (lane == leader) {
-                    unsafeAtomicAdd(mapb + lc, v0);
-                    if (a.npol == 2) unsafeAtomicAdd(mapb + a.map_stride + lc, v1);
-                }
-                if (mine) done = true;
-                pend &= ~grp;
+            } else if (cell >= 0) {
+                unsafeAtomicAdd(map + cell, w0);
+                if (two) unsafeAtomicAdd(map + a.map_stride + cell, w1);
             }
-        } else if (cell >= 0) {
-            unsafeAtomicAdd(mapb + cell, w0);
-            if (a.npol == 2) unsafeAtomicAdd(mapb + a.map_stride + cell, w1);
         }
 
         // ---- reflect, or end the ray
         if (active) {
-            if (slot < 0 || l == L) {
-                if (a.tape_nseg) a.tape_nseg[rid] = l + 1;
+            const FwdArgs& a = kernel_args();
+            if (slot < 0 || l == a.L) {
+                if (TAPE && a.tape_nseg) a.tape_nseg[rid] = l + 1;
                 active = false;
             } else {
                 float4 nm = a.normals[slot];
@@ -583,7 +836,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                 Bounce b = bounce_geometry(k, es, f3(nm.x, nm.y, nm.z));
                 int kind = 0;          // 0 specular reflection, 1 diffuse reflection, 2 transmission
                 float3 knew = b.kr, esnew = b.es_new;
-                if (MODE != MODE_GEOM) {
+                if (FIELDS) {
                     cf eta = cf{a.eps_r[mat], -a.sigma[mat] * a.pl.inv_eps0_omega};
                     Fresnel F = fresnel<false>(b.c, eta);
                     cf cperp = F.rperp, cpar = F.rpar;
@@ -620,59 +873,50 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                         }
                     }
                     if (EXT && kind == 1) {
-                        // diffuse reflection (Lambertian): direction drawn over
-                        // the hemisphere of the incident side, field scaled by
-                        // sqrt(2 cos(theta_s) S^2 Gamma^2 / q(S)) and mixed by
-                        // the cross-polarisation matrix with random phases, in
-                        // the theta/phi bases of the incident and new direction
-                        const cf e0 = cadd(cscale(Ta, c0t), cscale(Tb, c0p));
-                        const cf e1 = cadd(cscale(Tc, c0t), cscale(Td, c0p));
-                        const cf ap = cadd(cscale(e0, b.w00), cscale(e1, b.w01));
-                        const cf al = cadd(cscale(e0, b.w10), cscale(e1, b.w11));
-                        const float en2 = cabs2(e0) + cabs2(e1);
-                        const float g2 = en2 > 0.0f ? (cabs2(cmul(F.rperp, ap)) + cabs2(cmul(F.rpar, al))) / en2 : 0.0f;
-                        const uint4 w = philox4(a.seed, MODE == MODE_SINGLE ? a.ray_begin + rid : nlat, l, 2u);
-                        const float cs = word_uniform(w.x), ss = sqrtf(fmaxf(0.0f, 1.0f - cs * cs));
-                        float sph, cph, s1, c1, s2p, c2p;
-                        sincospif(2.0f * word_uniform(w.y), &sph, &cph);
-                        sincospif(2.0f * word_uniform(w.z), &s1, &c1);
-                        sincospif(2.0f * word_uniform(w.w), &s2p, &c2p);
-                        float3 n = f3(nm.x, nm.y, nm.z);
-                        if (dot3(k, n) > 0.0f) n = n * -1.0f;
-                        knew = diffuse_direction(n, cs, ss, cph, sph);
-                        float3 thi, phi_i, phs;
-                        sph_basis(k, thi, phi_i);
-                        sph_basis(knew, esnew, phs);
-                        const float3 ep = cross3(k, es);
-                        const float p00 = dot3(thi, es), p01 = dot3(thi, ep);
-                        const float p10 = dot3(phi_i, es), p11 = dot3(phi_i, ep);
-                        const float K = a.xpd[mat], sk = sqrtf(K), ck = sqrtf(1.0f - K);
-                        const float fw = scatter_weight(a.pattern ? a.pattern + 4 * mat : nullptr, b.c, cs, k, knew, b.kr);
-                        const float sc = sqrtf(fw * s2 * g2) * __builtin_amdgcn_rsqf(qs);
-                        const float a0 = ck * p00 - sk * p10, a1 = ck * p01 - sk * p11;   // theta row
-                        const float b0 = sk * p00 + ck * p10, b1 = sk * p01 + ck * p11;   // phi row
-                        const cf x1 = cf{c1 * sc, s1 * sc}, x2 = cf{c2p * sc, s2p * sc};
-                        const cf na = cmul(x1, cadd(cscale(Ta, a0), cscale(Tc, a1)));
-                        const cf nb = cmul(x1, cadd(cscale(Tb, a0), cscale(Td, a1)));
-                        const cf nc = cmul(x2, cadd(cscale(Ta, b0), cscale(Tc, b1)));
-                        const cf nd = cmul(x2, cadd(cscale(Tb, b0), cscale(Td, b1)));
-                        Ta = na;
-                        Tb = nb;
-                        Tc = nc;
-                        Td = nd;
+                        if constexpr (EXT && FIELD == 0) {
+                            // diffuse reflection (Lambertian): direction drawn over
+                            // the hemisphere of the incident side, field scaled by
+                            // sqrt(2 cos(theta_s) S^2 Gamma^2 / q(S)) and mixed by
+                            // the cross-polarisation matrix with random phases, in
+                            // the theta/phi bases of the incident and new direction
+                            const cf e0 = cadd(cscale(fs.Ta, fs.c0t), cscale(fs.Tb, fs.c0p));
+                            const cf e1 = cadd(cscale(fs.Tc, fs.c0t), cscale(fs.Td, fs.c0p));
+                            const cf ap = cadd(cscale(e0, b.w00), cscale(e1, b.w01));
+                            const cf al = cadd(cscale(e0, b.w10), cscale(e1, b.w11));
+                            const float en2 = cabs2(e0) + cabs2(e1);
+                            const float g2 = en2 > 0.0f ? (cabs2(cmul(F.rperp, ap)) + cabs2(cmul(F.rpar, al))) / en2 : 0.0f;
+                            const uint4 w = philox4(a.seed, MODE == MODE_SINGLE ? a.ray_begin + rid : nlat, l, 2u);
+                            const float cs = word_uniform(w.x), ss = sqrtf(fmaxf(0.0f, 1.0f - cs * cs));
+                            float sph, cph, s1, c1, s2p, c2p;
+                            sincospif(2.0f * word_uniform(w.y), &sph, &cph);
+                            sincospif(2.0f * word_uniform(w.z), &s1, &c1);
+                            sincospif(2.0f * word_uniform(w.w), &s2p, &c2p);
+                            float3 n = f3(nm.x, nm.y, nm.z);
+                            if (dot3(k, n) > 0.0f) n = n * -1.0f;
+                            knew = diffuse_direction(n, cs, ss, cph, sph);
+                            float3 thi, phi_i, phs;
+                            sph_basis(k, thi, phi_i);
+                            sph_basis(knew, esnew, phs);
+                            const float3 ep = cross3(k, es);
+                            const float p00 = dot3(thi, es), p01 = dot3(thi, ep);
+                            const float p10 = dot3(phi_i, es), p11 = dot3(phi_i, ep);
+                            const float K = a.xpd[mat], sk = sqrtf(K), ck = sqrtf(1.0f - K);
+                            const float fw = scatter_weight(a.pattern ? a.pattern + 4 * mat : nullptr, b.c, cs, k, knew, b.kr);
+                            const float sc = sqrtf(fw * s2 * g2) * __builtin_amdgcn_rsqf(qs);
+                            const float a0 = ck * p00 - sk * p10, a1 = ck * p01 - sk * p11;   // theta row
+                            const float b0 = sk * p00 + ck * p10, b1 = sk * p01 + ck * p11;   // phi row
+                            const cf x1 = cf{c1 * sc, s1 * sc}, x2 = cf{c2p * sc, s2p * sc};
+                            const cf na = cmul(x1, cadd(cscale(fs.Ta, a0), cscale(fs.Tc, a1)));
+                            const cf nb = cmul(x1, cadd(cscale(fs.Tb, a0), cscale(fs.Td, a1)));
+                            const cf nc = cmul(x2, cadd(cscale(fs.Ta, b0), cscale(fs.Tc, b1)));
+                            const cf nd = cmul(x2, cadd(cscale(fs.Tb, b0), cscale(fs.Td, b1)));
+                            fs.Ta = na;
+                            fs.Tb = nb;
+                            fs.Tc = nc;
+                            fs.Td = nd;
+                        }
                     } else {
-                        // T <- diag(c_perp, -c_par) W T: the new basis is
-                        // (e_perp, k' x e_perp), whose second vector is -e_par
-                        // of the outgoing wave for both k' = k_r and k' = k
-                        cf na = cadd(cscale(Ta, b.w00), cscale(Tc, b.w01));
-                        cf nb = cadd(cscale(Tb, b.w00), cscale(Td, b.w01));
-                        cf nc = cadd(cscale(Ta, b.w10), cscale(Tc, b.w11));
-                        cf nd = cadd(cscale(Tb, b.w10), cscale(Td, b.w11));
-                        Ta = cmul(cperp, na);
-                        Tb = cmul(cperp, nb);
-                        cf mr = cf{-cpar.re, -cpar.im};
-                        Tc = cmul(mr, nc);
-                        Td = cmul(mr, nd);
+                        fs.interact(b, cperp, cpar);
                     }
                 }
                 o = o + k * t_hit;
@@ -681,46 +925,49 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                 last = slot;
                 l++;
                 if (EXT) rlen = kind == 1 ? 0.0f : rlen + t_hit;   // a diffuse point starts a new tube
-                if (EXT && l >= a.rr_depth && (a.rr_p_max > 0.0f || a.gain_threshold > 0.0f)) {
-                    // early termination before segment l: the distance-normalised
-                    // gain ||T C||^2 of polarisation 0 (times |alpha|^2)
-                    const cf e0 = cadd(cscale(Ta, c0t), cscale(Tb, c0p));
-                    const cf e1 = cadd(cscale(Tc, c0t), cscale(Td, c0p));
-                    const float gn = (cabs2(e0) + cabs2(e1)) * (kap * (MODE == MODE_SINGLE ? a.inv_kappa : ikap));
-                    bool drop = false;
-                    if (a.gain_threshold > 0.0f && rlen > 0.0f)
-                        drop = a.gain_scale * gn * __builtin_amdgcn_rcpf(rlen * rlen) < a.gain_threshold;
-                    if (!drop && a.rr_p_max > 0.0f) {
-                        const float p = fminf(gn, a.rr_p_max);
-                        if (philox_uniform(a.seed, MODE == MODE_SINGLE ? a.ray_begin + rid : nlat, l, 0u) < p) {
-                            const float sc = __builtin_amdgcn_rsqf(p);   // survivors carry 1/sqrt(p)
-                            Ta = cscale(Ta, sc);
-                            Tb = cscale(Tb, sc);
-                            Tc = cscale(Tc, sc);
-                            Td = cscale(Td, sc);
-                        } else {
-                            drop = true;
+                if constexpr (EXT && FIELD == 0) {
+                    if (l >= a.rr_depth && (a.rr_p_max > 0.0f || a.gain_threshold > 0.0f)) {
+                        // early termination before segment l: the distance-normalised
+                        // gain ||T C||^2 of polarisation 0 (times |alpha|^2)
+                        const float gn = fs.power(0) * (kap * (MODE == MODE_SINGLE ? a.inv_kappa : ikap));
+                        bool drop = false;
+                        if (a.gain_threshold > 0.0f && rlen > 0.0f)
+                            drop = a.gain_scale * gn * __builtin_amdgcn_rcpf(rlen * rlen) < a.gain_threshold;
+                        if (!drop && a.rr_p_max > 0.0f) {
+                            const float p = fminf(gn, a.rr_p_max);
+                            if (philox_uniform(a.seed, MODE == MODE_SINGLE ? a.ray_begin + rid : nlat, l, 0u) < p) {
+                                const float sc = __builtin_amdgcn_rsqf(p);   // survivors carry 1/sqrt(p)
+                                fs.Ta = cscale(fs.Ta, sc);
+                                fs.Tb = cscale(fs.Tb, sc);
+                                fs.Tc = cscale(fs.Tc, sc);
+                                fs.Td = cscale(fs.Td, sc);
+                            } else {
+                                drop = true;
+                            }
                         }
-                    }
-                    if (drop) {
-                        active = false;
-                        if (a.tape_nseg) a.tape_nseg[rid] = l;   // segments 0..l-1 were traced
+                        if (drop) {
+                            active = false;
+                            if (TAPE && a.tape_nseg) a.tape_nseg[rid] = l;   // segments 0..l-1 were traced
+                        }
                     }
                 }
             }
         }
     }
 
-    if (a.stats) {
-        unsigned long long v[5] = {st_seg, st_cross, st_nodes, st_tris, st_over};
-        for (int i = 0; i < 5; i++) {
-            unsigned long long s = v[i];
-            for (int off = 32; off >= 1; off >>= 1) {
-                unsigned lo = __shfl_xor((unsigned)(s & 0xffffffffu), off);
-                unsigned hi = __shfl_xor((unsigned)(s >> 32), off);
-                s += ((unsigned long long)hi << 32) | lo;
+    if (REC) {
+        const FwdArgs& a = kernel_args();
+        if (a.stats) {
+            unsigned long long v[5] = {st_seg, st_cross, st_nodes, st_tris, st_over};
+            for (int i = 0; i < 5; i++) {
+                unsigned long long s = v[i];
+                for (int off = 32; off >= 1; off >>= 1) {
+                    unsigned lo = __shfl_xor((unsigned)(s & 0xffffffffu), off);
+                    unsigned hi = __shfl_xor((unsigned)(s >> 32), off);
+                    s += ((unsigned long long)hi << 32) | lo;
+                }
+                if (lane == 0 && s) atomicAdd(a.stats + i, s);
             }
-            if (lane == 0 && s) atomicAdd(a.stats + i, s);
         }
     }
 }
@@ -806,28 +1053,38 @@ static void launch_mode(const FwdArgs& args, int accel, bool wide, int blocks, i
     a.claim = 64 * (int)std::max<int64_t>(1, std::min<int64_t>(4, a.n_work / ((int64_t)blocks * block * 16)));
     if (const char* env = getenv("RTMAP_CLAIM"))
         a.claim = std::max(64, std::min(4096, atoi(env)));
-    size_t lds = sizeof(int2) * RT_STACK_LDS * block;   // {node, entry distance} per entry
-    if constexpr (MODE != MODE_GEOM) {
-        if (ext) {
-            if constexpr (MODE == MODE_SINGLE) {
-                if (accel == RT_ACCEL_BRUTE) {
-                    hipLaunchKernelGGL((k_forward<true, MODE, false, true>), dim3(blocks), dim3(block), lds, st, a);
-                    return;
-                }
-            }
-            if (wide)
-                hipLaunchKernelGGL((k_forward<false, MODE, true, true>), dim3(blocks), dim3(block), lds, st, a);
-            else
-                hipLaunchKernelGGL((k_forward<false, MODE, false, true>), dim3(blocks), dim3(block), lds, st, a);
-            return;
-        }
+    const size_t lds = sizeof(int2) * RT_STACK_LDS * block;   // {node, entry distance} per entry
+    // calls with records, statistics or a tape, and the extensions, carry the
+    // transfer matrix; the others the fields themselves
+    [[maybe_unused]] const bool rec = a.hits || a.cells || a.weights || a.stats || (MODE == MODE_SINGLE && a.tape_seg);
+    [[maybe_unused]] const bool two = a.npol == 2;
+#define RT_LAUNCH(BRUTE, WIDE, EXT, REC, FIELD) \
+    hipLaunchKernelGGL((k_forward<BRUTE, MODE, WIDE, EXT, REC, FIELD>), dim3(blocks), dim3(block), lds, st, a)
+    if constexpr (MODE == MODE_GEOM) {
+        if (wide) RT_LAUNCH(false, true, false, false, 1);
+        else RT_LAUNCH(false, false, false, false, 1);
+    } else if constexpr (MODE == MODE_MULTI) {
+        if (ext && wide) RT_LAUNCH(false, true, true, false, 0);
+        else if (ext) RT_LAUNCH(false, false, true, false, 0);
+        else if (wide) RT_LAUNCH(false, true, false, false, 1);
+        else RT_LAUNCH(false, false, false, false, 1);
+    } else if (accel == RT_ACCEL_BRUTE) {
+        if (ext) RT_LAUNCH(true, false, true, true, 0);
+        else RT_LAUNCH(true, false, false, true, 0);
+    } else if (!wide) {
+        if (ext) RT_LAUNCH(false, false, true, true, 0);
+        else RT_LAUNCH(false, false, false, true, 0);
+    } else if (ext) {
+        if (rec) RT_LAUNCH(false, true, true, true, 0);
+        else RT_LAUNCH(false, true, true, false, 0);
+    } else if (rec) {
+        RT_LAUNCH(false, true, false, true, 0);
+    } else if (two) {
+        RT_LAUNCH(false, true, false, false, 2);
+    } else {
+        RT_LAUNCH(false, true, false, false, 1);
     }
-    if (accel == RT_ACCEL_BRUTE)
-        hipLaunchKernelGGL((k_forward<true, MODE, false, false>), dim3(blocks), dim3(block), lds, st, a);
-    else if (wide)
-        hipLaunchKernelGGL((k_forward<false, MODE, true, false>), dim3(blocks), dim3(block), lds, st, a);
-    else
-        hipLaunchKernelGGL((k_forward<false, MODE, false, false>), dim3(blocks), dim3(block), lds, st, a);
+#undef RT_LAUNCH
 }
 
 // Tree width: forced by accel, else tuned (or overridden), default 4-wide.

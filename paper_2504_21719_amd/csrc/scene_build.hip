@@ -454,7 +454,8 @@ __global__ void k_wide_emit(const int4* __restrict__ child, const float4* __rest
     }
     w[6] = make_float4(__int_as_float(out[0]), __int_as_float(out[1]), __int_as_float(out[2]),
                        __int_as_float(out[3]));
-    w[7] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int leaf = (out[0] < 0 ? 2 : 0) | (out[1] < 0 ? 4 : 0) | (out[2] < 0 ? 8 : 0) | (out[3] < 0 ? 16 : 0);
+    w[7] = make_float4(__int_as_float(leaf), 0.0f, 0.0f, 0.0f);
 }
 
 __global__ void k_flags_to_u32(const int* __restrict__ f, unsigned* __restrict__ u, int64_t n) {
