@@ -458,8 +458,8 @@ def manhattan_leg(rt, cfg, scene, eps, sig, out, tune_s, dev, reps=20):
 
 def kernel_ms(rt, scene, eps, sig, cfg, out, stream, steps):
     """Average duration of the forward launch alone: with accumulate = 1 a call
-    queues only the work-counter reset (one thread) and the launch-order
-    rotations (a few hundred threads) besides the forward kernel."""
+    queues only the work-counter reset (a few hundred threads) besides the
+    forward kernel."""
     import numpy as np
     import torch
     evk = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(steps)]

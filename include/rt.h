@@ -42,8 +42,8 @@
  *   - The library never takes ownership of caller memory.  Objects it creates
  *     (rt_scene, rt_tape) are released only by their destroy calls.
  *   - Calls on one rt_scene share its device work state (work-queue
- *     counters, traversal spill area, launch-order tables, workspaces and
- *     the captured batched graph): queue them on one stream, or order them
+ *     counters, traversal spill area, workspaces and the captured batched
+ *     graph): queue them on one stream, or order them
  *     across streams and host threads; calls on different scenes are
  *     independent.  Likewise a tape belongs to one forward-backward pair at
  *     a time.
@@ -479,8 +479,8 @@ rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials materials,
  * block_size 0).
  * Writes the chosen block size and deposit strategy (host ints, may be NULL);
  * rt_scene_info_get reports the whole choice.
- * Launch order: by default each chunk of consecutive lattice indices is
- * launched sorted by azimuth, so that a wavefront starts on a small patch of
+ * Launch order: by default each chunk of consecutive lattice indices (a
+ * Fibonacci number of them) is launched sorted by azimuth, so that a wavefront starts on a small patch of
  * directions (results are unchanged up to FP32 summation order).
  * Synchronises `stream`; `scratch_map` is device float32 of the map's size
  * and is overwritten.

@@ -96,11 +96,6 @@ extern "C" rt_status rt_scene_destroy(rt_scene* s) {
     (void)hipFree(s->spill);
     (void)hipFree(s->tx_desc);
     (void)hipFree(s->grad_ws);
-    for (int i = 0; i < s->n_otab; i++) {
-        (void)hipFree(s->otab[i].perm);
-        (void)hipFree(s->otab[i].az);
-    }
-    (void)hipFree(s->shifts);
     (void)hipFree(s->geom_ws);
     (void)hipFree(s->bgrad_ws);
     if (s->tx_desc_host) (void)hipHostFree(s->tx_desc_host);
@@ -325,17 +320,6 @@ static bool want_order(const rt_scene* s) {
     return s->tuned_order != 2;
 }
 
-// Launch-order table for an N-ray lattice and room for its chunk rotations
-// (synchronous on first use of a chunk size or a larger lattice).
-static rt_status prepare_order(rt_scene* s, int64_t N, size_t chunks_total, int log2m, hipStream_t st,
-                               const rt_scene::OrderTable** out) {
-    *out = nullptr;
-    if (!want_order(s) || N < 4096) return RT_OK;
-    rt_status r = rt_order_table(s, log2m, st, out);
-    if (r != RT_OK) return r;
-    return rt_order_reserve(s, chunks_total, st);
-}
-
 static rt_status check_device(const rt_scene* s) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -383,12 +367,7 @@ extern "C" rt_status rt_radio_map(const rt_scene* scene, rt_materials materials,
     f.deposit = pick_deposit(scene, params);
     f.block = pick_block(scene, params);
     f.refill = pick_refill(scene);
-    {
-        int l = rt_order_log2m(params->n_rays);
-        rt_status ro = prepare_order(const_cast<rt_scene*>(scene), params->n_rays,
-                                     (size_t)(params->n_rays >> l), l, (hipStream_t)stream, &f.order);
-        if (ro != RT_OK) return ro;
-    }
+    f.tx.order = rt_launch_order(e - b, params->n_rays, want_order(scene));
     f.zero_map = params->accumulate == 0;
     f.map = out_map;
     f.tape = tape;
@@ -583,16 +562,10 @@ extern "C" rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials ma
     int64_t* hw = hp + (n_tx + 1);
     int32_t* hslot = (int32_t*)(hw + (n_tx + 1));
     int64_t total = 0;
-    // one launch-order chunk size for the whole batch (from the largest lattice)
-    const int olog2m = rt_order_log2m(rays_per_tx[order[0]]);
-    int64_t chunks_total = 0, max_chunks = 0;
     for (int i = 0; i < n_tx; i++) {
         int t = order[i];
         fill_tx(&txs[t], rays_per_tx[t], plane, params->freq_hz, &hd[i]);
-        hd[i].n_chunks = rays_per_tx[t] >> olog2m;
-        hd[i].shift0 = chunks_total;
-        chunks_total += hd[i].n_chunks;
-        max_chunks = std::max(max_chunks, hd[i].n_chunks);
+        hd[i].order = rt_launch_order(rays_per_tx[t], rays_per_tx[t], want_order(s));
         hp[i] = total;
         hslot[i] = t;
         total += rays_per_tx[t];
@@ -603,15 +576,6 @@ extern "C" rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials ma
     // (transmitter, wavefront) and add them in order
     hw[0] = 0;
     for (int i = 0; i < n_tx; i++) hw[i + 1] = hw[i] + (hp[i + 1] - 1) / 64 - hp[i] / 64 + 1;
-    const rt_scene::OrderTable* otab = nullptr;
-    {
-        rt_status ro = prepare_order(s, rays_per_tx[order[0]], (size_t)chunks_total, olog2m, hs, &otab);
-        if (ro != RT_OK) return ro;
-        if (!otab) {
-            for (int i = 0; i < n_tx; i++) hd[i].n_chunks = 0;
-            max_chunks = 0;
-        }
-    }
     BatchLaunch bl{};
     bl.scene = scene;
     bl.eps_r = materials.eps_r;
@@ -626,8 +590,6 @@ extern "C" rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials ma
     bl.block = pick_block(scene, params);
     bl.deposit = pick_deposit(scene, params);
     bl.refill = pick_refill(scene);
-    bl.order = otab;
-    bl.max_chunks = max_chunks;
     bl.maps = out_maps;
     bl.grad_maps = grad_maps;
     bl.grads = grads;
@@ -667,7 +629,7 @@ extern "C" rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials ma
     key = mix(key, &params->freq_hz, sizeof(double));
     key = mix(key, &bl.deposit, sizeof(int));
     key = mix(key, &bl.refill, sizeof(int));
-    const void* ws[6] = {otab, s->shifts, s->tx_desc, s->geom_ws, s->bgrad_ws, s->wide};
+    const void* ws[4] = {s->tx_desc, s->geom_ws, s->bgrad_ws, s->wide};
     key = mix(key, ws, sizeof(ws));
     int width = s->tuned_width;
     if (const char* env = getenv("RTMAP_WIDTH")) width = atoi(env);
@@ -747,10 +709,10 @@ extern "C" rt_status rt_tune(rt_scene* scene, rt_materials materials, const rt_t
     rt_status r = check_params(params, &b0, &e0r);
     if (r != RT_OK) return r;
     hipStream_t st = (hipStream_t)stream;
-    // probe: eight sub-ranges spread evenly over the lattice, aligned to the
-    // launch-order chunks, so that every direction band is represented
+    // probe: eight sub-ranges of whole launch-order chunks spread evenly over
+    // the lattice, so that every direction band is represented
     const int64_t N = params->n_rays;
-    const int64_t M = (int64_t)1 << rt_order_log2m(N);
+    const int64_t M = rt_order_chunk(rt_launch_order(N, N, true));
     const int n_sub = 8;
     int64_t sub = std::min<int64_t>(N, std::max<int64_t>(M, ((n_probe_rays / n_sub + M - 1) / M) * M));
     std::vector<std::pair<int64_t, int64_t>> ranges;
@@ -799,7 +761,7 @@ extern "C" rt_status rt_tune(rt_scene* scene, rt_materials materials, const rt_t
                         scene->tuned_refill = ri;
                         scene->tuned_order = oi;
                         scene->tuned_width = wi;
-                        r = run_once();   // warm-up (also builds order tables)
+                        r = run_once();   // warm-up
                         if (r != RT_OK) break;
                         float ts[3] = {0, 0, 0};
                         for (int rep = 0; rep < 3 && r == RT_OK; rep++) {

@@ -73,17 +73,6 @@ struct rt_scene {
     int tuned_deposit = 0;
     int tuned_refill = 0;     // refill a wavefront once this many lanes are idle
     int tuned_order = 0;      // 1 coherent launch order, 2 lattice order
-    // coherent launch order: per chunk size 2^log2m, the azimuth-sorted order
-    // of j in [0, 2^log2m) (perm) and its sorted azimuths (az); any chunk's
-    // order is a rotation of it (see rt_order_table)
-    struct OrderTable {
-        int log2m = 0;
-        int* perm = nullptr;
-        unsigned* az = nullptr;
-    } otab[12];
-    int n_otab = 0;
-    int* shifts = nullptr;          // per-call rotation of every full chunk
-    size_t shifts_cap = 0;
     // backward workspace: per-block FP64 partial sums
     void* grad_ws = nullptr;
     size_t grad_ws_bytes = 0;
@@ -120,6 +109,24 @@ struct rt_tape {
     bool filled = false;
 };
 
+// Coherent launch order of a run of consecutive lattice indices.  Any F
+// consecutive indices, F a Fibonacci number, come in ascending azimuth (up to
+// where the circle is cut) as base + (r F' mod F), r = 0..F - 1, with F' the
+// inverse of the preceding Fibonacci number modulo F: the azimuth step of the
+// lattice, phi_g - 1, is so near the ratio of the two that the order of the
+// multiples is theirs.  The run is cut into chunks of one F, whose size makes
+// the patch of a wavefront about as wide as high, and the rest into smaller
+// ones, largest first; what then remains is launched in lattice order.  A lane
+// computes its index (about 30 instructions per ray): against a sorted table
+// of one chunk, rotated per chunk by a small kernel, this takes two dependent
+// loads out of each refill and a launch out of each call (smallest call, 1e5
+// rays: 33 -> 24 us; first call on a new scene: no sort, no allocation).
+struct LaunchOrder {
+    int64_t full;            // indices in whole chunks
+    int32_t chunk;           // index of the chunk size in the Fibonacci table, 0 = lattice order
+    uint32_t tail;           // bit i: a chunk of size i of the table follows (largest first)
+};
+
 // Per-transmitter launch descriptor (host-computed constants).
 struct TxDesc {
     float pos[3];
@@ -131,8 +138,7 @@ struct TxDesc {
     float q;
     int32_t pol;             // 0 V, 1 H, 2 dual
     int64_t n_rays;          // N_S of this transmitter's lattice
-    int64_t shift0;          // first entry of this lattice's chunks in the shift table
-    int64_t n_chunks;        // full chunks of the launch order (0 = lattice order)
+    LaunchOrder order;       // launch order of the rays to trace
     float kappa;             // lambda^2 / (4 pi N_S dx dy)
     int32_t n_ant;           // synthetic transmit array (0 = single element)
     const double* ant_pos;   // [n_ant][3] element offsets, metres, global frame
@@ -169,7 +175,6 @@ struct FwdLaunch {
     int deposit;             // 1 atomic, 2 wave
     int block;
     int refill;              // 1..64
-    const rt_scene::OrderTable* order;   // coherent launch order, or null
     bool zero_map;
     float* map;
     rt_tape* tape;
@@ -257,8 +262,6 @@ struct BatchLaunch {
     int block;
     int deposit;
     int refill;
-    const rt_scene::OrderTable* order;   // coherent launch order, or null
-    int64_t max_chunks;      // largest number of full chunks of one lattice
     float* maps;             // [n_tx][S][H][W]
     const float* grad_maps;  // [n_tx][S][H][W] or null
     float* grads;            // [n_tx][S][2 n_mat + 3] or null
@@ -271,9 +274,8 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st);
 
 rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const float* sigma, const PlaneDesc& pl,
                                   int L, float t_min, int block, int deposit, int refill,
-                                  const rt_scene::OrderTable* order, int64_t max_chunks, const TxDesc* txs,
-                                  const int64_t* prefix, const int32_t* slots, int n_tx, int64_t total_rays,
-                                  bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
+                                  const TxDesc* txs, const int64_t* prefix, const int32_t* slots, int n_tx,
+                                  int64_t total_rays, bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
                                   float4* geom_seg, int* geom_nseg, const FwdExt* ext, hipStream_t st);
 
 int rt_persistent_blocks(int block, int device);
@@ -283,13 +285,8 @@ int rt_persistent_blocks(int block, int device);
 // level spans at least one binary level.
 inline int64_t rt_stack_need(const rt_scene* s) { return 3 * (int64_t)s->depth + 2; }
 
-// Coherent launch order.  rt_order_log2m picks the chunk size for an N-ray
-// lattice; rt_order_table builds (once, synchronously) the sorted order of a
-// chunk; rt_order_reserve grows the shift table (synchronously, outside any
-// capture); rt_order_shifts_* queue the per-chunk rotations.
-int rt_order_log2m(int64_t N);
-rt_status rt_order_table(rt_scene* s, int log2m, hipStream_t st, const rt_scene::OrderTable** out);
-rt_status rt_order_reserve(rt_scene* s, size_t entries, hipStream_t st);
-void rt_order_shifts_single(const rt_scene::OrderTable* t, int64_t N, int* shifts, hipStream_t st);
-void rt_order_shifts_multi(const rt_scene::OrderTable* t, const TxDesc* txs, int n_tx, int64_t max_chunks,
-                           int* shifts, hipStream_t st);
+// Launch order of `count` consecutive indices of an N-ray lattice
+// (coherent = false: lattice order).
+LaunchOrder rt_launch_order(int64_t count, int64_t N, bool coherent);
+// Size of its chunks (1 in lattice order).
+int64_t rt_order_chunk(const LaunchOrder& o);

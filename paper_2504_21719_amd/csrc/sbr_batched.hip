@@ -68,21 +68,7 @@ struct SampArgs {
     int P;                  // 2 n_mat + 3
     const float* thickness; // slab thickness per material (m, shared by the samples), or null
     float k0;               // 2 pi / lambda
-    // launch order of the geometry tape: record g of transmitter t holds work
-    // item n = g - prefix[t], whose lattice index is the chunk permutation of n
-    const int* operm;       // null: records are in lattice order
-    const int* oshift;
-    int olog2m;
 };
-
-// Lattice index of work item n of transmitter td (the forward's launch order).
-__device__ __forceinline__ int64_t lattice_index(const SampArgs& a, const TxDesc& td, int64_t n) {
-    if (a.operm && (n >> a.olog2m) < td.n_chunks) {
-        const int64_t M = (int64_t)1 << a.olog2m, c = n >> a.olog2m, c0 = c << a.olog2m;
-        n = c0 + a.operm[((n - c0) + a.oshift[td.shift0 + c]) & (M - 1)];
-    }
-    return n;
-}
 
 __device__ __forceinline__ float wave_sum_f(float v) {
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
@@ -173,7 +159,8 @@ __global__ void __launch_bounds__(kSampBlock) k_samples(const SampArgs a) {
                 tx_i = t;
                 slot_out = a.slots[t];
                 ns = a.nseg[g];
-                const int64_t n = lattice_index(a, td, g - a.prefix[t]);
+                // the geometry tape is in launch order
+                const int64_t n = launch_index(td.order, g - a.prefix[t]);
                 Launch Lr = fib_launch(n, td.n_rays);
                 if (GRAD) {
                     tx_pattern<d3f>(Lr, td, td.pol == 1 ? 1 : 0, cth, cph);
@@ -378,7 +365,7 @@ __global__ void __launch_bounds__(kSampBlock) k_samples_deep(const SampArgs a) {
         const TxDesc td = a.txs[t];
         const int slot_out = a.slots[t];
         const int ns = a.nseg[g];
-        const int64_t nl = lattice_index(a, td, g - a.prefix[t]);
+        const int64_t nl = launch_index(td.order, g - a.prefix[t]);
         const float* eps = a.eps_r + (int64_t)s * a.n_mat;
         const float* sig = a.sigma + (int64_t)s * a.n_mat;
         float* map = a.maps + ((int64_t)slot_out * a.S + s) * HW;
@@ -477,8 +464,7 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st) {
     const bool grad = b.grad_maps != nullptr;
     if (S == 1 && !grad) {
         return rt_launch_forward_multi(s, b.eps_r, b.sigma, b.pl, b.L, b.t_min, b.block, b.deposit, b.refill,
-                                       b.order, b.max_chunks, b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx,
-                                       b.total_rays, false, b.maps, HW, HW * b.n_tx, nullptr, nullptr, &b.ext, st);
+                                       b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx, b.total_rays, false, b.maps, HW, HW * b.n_tx, nullptr, nullptr, &b.ext, st);
     }
     size_t need = sizeof(float4) * 2 * (size_t)(b.L + 1) * (size_t)b.total_rays + sizeof(int) * (size_t)b.total_rays;
     const int P = 2 * s->n_mat + 3;
@@ -487,8 +473,7 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st) {
     float4* geom = (float4*)s->geom_ws;
     int* nseg = (int*)((char*)s->geom_ws + sizeof(float4) * 2 * (size_t)(b.L + 1) * (size_t)b.total_rays);
     rt_status r = rt_launch_forward_multi(s, b.eps_r, b.sigma, b.pl, b.L, b.t_min, b.block, b.deposit, b.refill,
-                                          b.order, b.max_chunks, b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx,
-                                          b.total_rays, true, b.maps, HW, HW * b.n_tx * S, geom, nseg, nullptr, st);
+                                          b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx, b.total_rays, true, b.maps, HW, HW * b.n_tx * S, geom, nseg, nullptr, st);
     if (r != RT_OK) return r;
     SampArgs a;
     a.geom = geom;
@@ -511,9 +496,6 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st) {
     a.P = P;
     a.thickness = b.ext.thickness;
     a.k0 = b.ext.k0;
-    a.operm = b.order ? b.order->perm : nullptr;
-    a.oshift = s->shifts;
-    a.olog2m = b.order ? b.order->log2m : 0;
     unsigned bx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1 << 20, (b.total_rays + 63) / 64));
     const unsigned sblock = 64u * (unsigned)std::min(4, S);   // wavefronts of one 64-ray group, one per sample
     if (b.total_rays > 0) {

@@ -20,6 +20,61 @@ namespace rtd {
 // round(2^64 (phi_g - 1)): frac(n / phi_g) = frac(n (phi_g - 1)) = (n * C mod 2^64) / 2^64
 constexpr uint64_t kPhiFrac = 0x9e3779b97f4a7c16ull;
 
+// Fibonacci numbers F = 1, 2, 3, 5, ... up to 2,178,309 with, for the launch
+// order, 1 / F and the inverse of the preceding number modulo F.
+constexpr int kFibCount = 31;
+struct FibEntry {
+    int size, inv;
+    double rcp;
+};
+struct FibTable {
+    FibEntry e[kFibCount];
+};
+constexpr FibTable make_fib_table() {
+    FibTable t{};
+    t.e[0].size = 1;
+    t.e[1].size = 2;
+    for (int i = 2; i < kFibCount; i++) t.e[i].size = t.e[i - 1].size + t.e[i - 2].size;
+    for (int i = 0; i < kFibCount; i++) t.e[i].rcp = 1.0 / (double)t.e[i].size;
+    for (int i = 1; i < kFibCount; i++) {
+        const int64_t F = t.e[i].size, p = t.e[i - 1].size;
+        t.e[i].inv = (int)(p * p % F == 1 % F ? p : F - p);     // p^2 = +-1 (mod F)
+    }
+    return t;
+}
+static __constant__ const FibTable kFib = make_fib_table();
+
+// v mod F for 0 <= v < 2^53 whole, with the quotient below 2^31: the rounded
+// quotient is off by one at most.
+__device__ __forceinline__ int fib_mod(double v, const FibEntry& f) {
+    const double q = __builtin_trunc(v * f.rcp);
+    const int d = (int)__builtin_fma(-q, (double)f.size, v);
+    return d < 0 ? d + f.size : d >= f.size ? d - f.size : d;
+}
+
+// Lattice index (relative to the start of the run) of launch index n < 2^40.
+__device__ __forceinline__ int64_t launch_index(const LaunchOrder& o, int64_t n) {
+    int i = o.chunk, r;
+    if (i == 0) return n;
+    if (n < o.full) {
+        r = fib_mod((double)n, kFib.e[i]);
+    } else {
+        int64_t base = o.full;
+        unsigned left = o.tail;
+        i = 0;
+        while (left) {
+            i = 31 - __clz(left);
+            if (n < base + kFib.e[i].size) break;
+            base += kFib.e[i].size;
+            left ^= 1u << i;
+            i = 0;
+        }
+        if (i == 0) return n;
+        r = (int)(n - base);
+    }
+    return n - r + fib_mod((double)r * (double)kFib.e[i].inv, kFib.e[i]);
+}
+
 // ---------------------------------------------------------------- duals
 // FP32 forward-mode scalar carrying d/d(yaw, pitch, roll).
 struct d3f {

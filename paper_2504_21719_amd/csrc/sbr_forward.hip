@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cfloat>
+#include <cmath>
 #include <cstring>
 
 #include "sbr_common.h"
@@ -87,10 +88,6 @@ struct FwdArgs {
     int64_t spill_stride;
     int spill_depth;
     int tape_groups;         // float4 records per segment on the tape (4, or 2 = geometry only)
-    const int* operm;        // coherent launch order: sorted chunk order, or null
-    const int* oshift;       // rotation of every full chunk
-    int olog2m;              // chunk size 2^olog2m
-    int64_t ray_end;
     int refill;              // refill a wavefront once this many lanes are idle
     // several transmitters (MODE_MULTI, MODE_GEOM): device tables
     const TxDesc* txs;       // ordered largest budget first
@@ -666,29 +663,18 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                         rid = (int64_t)my;
                         int64_t n;
                         const TxDesc* tp;
-                        const int64_t M = (int64_t)1 << a.olog2m;
                         if (MODE == MODE_SINGLE) {
+                            rid = launch_index(a.tx.order, rid);   // records stay indexed by lattice index
                             n = a.ray_begin + rid;
-                            if (a.operm) {
-                                // permuted only inside full chunks that the range covers
-                                int64_t c = n >> a.olog2m, c0 = c << a.olog2m;
-                                if (c < (a.tx.n_rays >> a.olog2m) && c0 >= a.ray_begin && c0 + M <= a.ray_end)
-                                    n = c0 + a.operm[((n - c0) + a.oshift[c]) & (M - 1)];
-                            }
-                            rid = n - a.ray_begin;   // records stay indexed by lattice index
                             tp = &a.tx;
                         } else {
                             int t = find_tx(a.prefix, a.n_tx, rid);
-                            n = rid - a.prefix[t];
                             tp = a.txs + t;
-                            if (a.operm && (n >> a.olog2m) < tp->n_chunks) {
-                                int64_t c = n >> a.olog2m, c0 = c << a.olog2m;
-                                n = c0 + a.operm[((n - c0) + a.oshift[tp->shift0 + c]) & (M - 1)];
-                                // the geometry tape stays in launch order (a
-                                // wavefront of the field pass then reads
-                                // consecutive records of nearby directions)
-                                if (MODE != MODE_GEOM) rid = a.prefix[t] + n;
-                            }
+                            n = launch_index(tp->order, rid - a.prefix[t]);
+                            // the geometry tape stays in launch order (a
+                            // wavefront of the field pass then reads
+                            // consecutive records of nearby directions)
+                            if (MODE != MODE_GEOM) rid = a.prefix[t] + n;
                             mapb = a.map + (int64_t)a.slots[t] * a.slot_stride;
                             nlat = n;
                             ikap = 1.0f / tp->kappa;
@@ -984,6 +970,37 @@ __global__ void k_prepare(float* __restrict__ map, int64_t n, unsigned long long
 
 }  // namespace
 
+// Fewer indices than this are launched in lattice order.
+static constexpr int64_t kOrderMin = 512;
+// Smallest chunk of the rest: a wavefront of it spans less than half a turn.
+static constexpr int kOrderTailMin = 10;      // 144
+
+LaunchOrder rt_launch_order(int64_t count, int64_t N, bool coherent) {
+    constexpr FibTable fib = make_fib_table();
+    LaunchOrder o{0, 0, 0};
+    if (!coherent || count < kOrderMin) return o;
+    // wave patches of roughly equal extent in polar and azimuthal angle: a
+    // chunk spans 2 F / N in z, a wave 2 pi 64 / F in azimuth -> F^2 ~ 64 pi N
+    const double want = std::sqrt(64.0 * RT_PI * (double)N);
+    int i = kOrderTailMin;
+    while (i + 1 < kFibCount && want * want > (double)fib.e[i].size * (double)fib.e[i + 1].size) i++;
+    while (i > kOrderTailMin && (int64_t)fib.e[i].size > count) i--;
+    o.chunk = i;
+    o.full = count / fib.e[i].size * fib.e[i].size;
+    int64_t rest = count - o.full;
+    for (int j = i - 1; j >= kOrderTailMin; j--)
+        if (rest >= (int64_t)fib.e[j].size) {
+            o.tail |= 1u << j;
+            rest -= fib.e[j].size;
+        }
+    return o;
+}
+
+int64_t rt_order_chunk(const LaunchOrder& o) {
+    constexpr FibTable fib = make_fib_table();
+    return o.chunk ? (int64_t)fib.e[o.chunk].size : 1;
+}
+
 int rt_persistent_blocks(int block, int device) {
     static int cu[64] = {0};
     int dev = device < 64 ? device : 0;
@@ -1114,12 +1131,6 @@ rt_status rt_launch_forward(const FwdLaunch& f, hipStream_t st) {
     a.weights = f.weights;
     a.stats = f.stats;
     a.refill = std::max(1, std::min(64, f.refill));
-    a.ray_end = f.ray_end;
-    if (f.order) {
-        a.operm = f.order->perm;
-        a.oshift = s->shifts;
-        a.olog2m = f.order->log2m;
-    }
     int blocks = 0;
     rt_status r = size_spill(a, s, f.block, &blocks);
     if (r != RT_OK) return r;
@@ -1129,7 +1140,6 @@ rt_status rt_launch_forward(const FwdLaunch& f, hipStream_t st) {
         int g = (int)std::min<int64_t>(2048, std::max<int64_t>(2, (zn + 255) / 256));
         hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, f.map, zn, s->counters);
     }
-    if (f.order) rt_order_shifts_single(f.order, f.tx.n_rays, s->shifts, st);
     a.rr_depth = f.rr_depth;
     a.rr_p_max = f.rr_p_max;
     a.gain_threshold = f.gain_threshold;
@@ -1154,9 +1164,8 @@ rt_status rt_launch_forward(const FwdLaunch& f, hipStream_t st) {
 // here); geom_only = true: write the geometry tape (2 records per segment).
 rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const float* sigma, const PlaneDesc& pl,
                                   int L, float t_min, int block, int deposit, int refill,
-                                  const rt_scene::OrderTable* order, int64_t max_chunks, const TxDesc* txs,
-                                  const int64_t* prefix, const int32_t* slots, int n_tx, int64_t total_rays,
-                                  bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
+                                  const TxDesc* txs, const int64_t* prefix, const int32_t* slots, int n_tx,
+                                  int64_t total_rays, bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
                                   float4* geom_seg, int* geom_nseg, const FwdExt* ext, hipStream_t st) {
     FwdArgs a;
     base_args(a, s, block, eps_r, sigma, pl, L, t_min);
@@ -1171,11 +1180,6 @@ rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const f
     a.n_tx = n_tx;
     a.slot_stride = slot_stride;
     a.refill = std::max(1, std::min(64, refill));
-    if (order) {
-        a.operm = order->perm;
-        a.oshift = s->shifts;
-        a.olog2m = order->log2m;
-    }
     if (geom_only) {
         a.tape_seg = geom_seg;
         a.tape_nseg = geom_nseg;
@@ -1187,7 +1191,6 @@ rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const f
     if (r != RT_OK) return r;
     int g = (int)std::min<int64_t>(4096, std::max<int64_t>(2, (zero_floats + 255) / 256));
     hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, maps, zero_floats, s->counters);
-    if (order) rt_order_shifts_multi(order, txs, n_tx, max_chunks, s->shifts, st);
     bool use_ext = false;
     if (ext && !geom_only) {
         a.rr_depth = ext->rr_depth;

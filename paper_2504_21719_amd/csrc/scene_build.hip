@@ -492,50 +492,6 @@ __global__ void k_gather(const float4* __restrict__ raw, const uint32_t* __restr
 
 inline unsigned grid_for(int64_t n, int block) { return (unsigned)std::max<int64_t>(1, (n + block - 1) / block); }
 
-// Sort key of lattice index n for the coherent launch order: the chunk
-// (M consecutive indices, i.e. a thin band of polar angle) in the high bits,
-// the Fibonacci azimuth frac(n (phi_g - 1)) in the low 32 bits.
-__global__ void k_order_keys(int64_t N, int64_t M, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-    int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    uint64_t az = ((uint64_t)n * 0x9e3779b97f4a7c16ull) >> 32;
-    keys[n] = ((uint64_t)(n / M) << 32) | az;
-    vals[n] = (uint32_t)n;
-}
-
-__global__ void k_low32(const uint64_t* __restrict__ k, unsigned* __restrict__ out, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (unsigned)(k[i] & 0xffffffffu);
-}
-
-// Rotation of every full chunk c of a lattice: the azimuths of the rays
-// c M + j are those of j shifted by the (fixed-point) azimuth of c M, so the
-// chunk's sorted order starts at the first sorted j whose azimuth is at
-// least 2^32 minus that shift.  (Carries from the low 32 bits are ignored:
-// the order only needs to be nearly sorted.)
-__global__ void k_order_shifts(const TxDesc* __restrict__ txs, int64_t N1, int log2m, const unsigned* __restrict__ az,
-                               int* __restrict__ shifts, int64_t max_chunks) {
-    int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t chunks, base;
-    if (txs) {
-        chunks = txs[blockIdx.y].n_chunks;
-        base = txs[blockIdx.y].shift0;
-    } else {
-        chunks = N1 >> log2m;
-        base = 0;
-    }
-    if (c >= chunks || c >= max_chunks) return;
-    unsigned off = (unsigned)(((uint64_t)(c << log2m) * 0x9e3779b97f4a7c16ull) >> 32);
-    unsigned target = 0u - off;
-    int lo = 0, hi = 1 << log2m;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (az[mid] < target) lo = mid + 1;
-        else hi = mid;
-    }
-    shifts[base + c] = (lo == (1 << log2m)) ? 0 : lo;
-}
-
 }  // namespace
 
 // Tile sums needed by scan_exclusive for `count` values.
@@ -556,113 +512,6 @@ void scan_exclusive(unsigned* data, int64_t count, unsigned* sums, hipStream_t s
 int64_t rs_hist_len(int64_t n) {
     const int64_t cells = 256 * ((n + kRsTile - 1) / kRsTile);
     return cells + scan_sums_len(cells);
-}
-
-// LSD radix sort of (key, value) pairs on the low `bits` bits of the keys.
-// Results end in (k0, v0) when the number of 8-bit passes is even, else in
-// (k1, v1); the return value says which (0 or 1).
-int rt_radix_sort(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1, int64_t n, int bits, unsigned* hist,
-                  hipStream_t st) {
-    const int rs_blocks = (int)((n + kRsTile - 1) / kRsTile);
-    uint64_t *ka = k0, *kb = k1;
-    uint32_t *va = v0, *vb = v1;
-    int which = 0;
-    for (int shift = 0; shift < bits; shift += 8) {
-        hipLaunchKernelGGL(k_rs_hist, dim3(rs_blocks), dim3(kBlock), 0, st, ka, n, shift, hist, rs_blocks);
-        scan_exclusive(hist, (int64_t)256 * rs_blocks, hist + (int64_t)256 * rs_blocks, st);
-        hipLaunchKernelGGL(k_rs_scatter, dim3(rs_blocks), dim3(kBlock), 0, st, ka, va, kb, vb, n, shift, hist,
-                           rs_blocks);
-        std::swap(ka, kb);
-        std::swap(va, vb);
-        which ^= 1;
-    }
-    return which;
-}
-
-int rt_order_log2m(int64_t N) {
-    // wave patches of roughly equal extent in polar and azimuthal angle:
-    // a chunk spans 2M/N in z, a wave 2 pi 64/M in azimuth -> M^2 ~ 64 pi N
-    double m = std::sqrt(64.0 * 3.14159265358979 * (double)N);
-    int l = (int)std::lround(std::log2(std::max(m, 1.0)));
-    return std::max(12, std::min(18, l));
-}
-
-// Sorted azimuths of j in [0, 2^log2m): key = top 32 bits of j (phi_g - 1)
-// in 64-bit fixed point.
-rt_status rt_order_table(rt_scene* s, int log2m, hipStream_t st, const rt_scene::OrderTable** out) {
-    for (int i = 0; i < s->n_otab; i++)
-        if (s->otab[i].log2m == log2m) {
-            *out = &s->otab[i];
-            return RT_OK;
-        }
-    if (s->n_otab >= 12) return rt_fail(RT_EINVAL, "launch order: too many chunk sizes");
-    const int64_t M = (int64_t)1 << log2m;
-    uint64_t *k0 = nullptr, *k1 = nullptr;
-    uint32_t *v0 = nullptr, *v1 = nullptr;
-    unsigned *hist = nullptr, *az = nullptr;
-    const int rs_blocks = (int)((M + kRsTile - 1) / kRsTile);
-    bool keep = false;
-    auto cleanup = [&]() {
-        (void)hipFree(k0);
-        (void)hipFree(k1);
-        (void)hipFree(v1);
-        (void)hipFree(hist);
-        if (!keep) {
-            (void)hipFree(v0);
-            (void)hipFree(az);
-        }
-    };
-    HIPCHK(hipMalloc(&k0, sizeof(uint64_t) * M));
-    HIPCHK(hipMalloc(&k1, sizeof(uint64_t) * M));
-    HIPCHK(hipMalloc(&v0, sizeof(uint32_t) * M));
-    HIPCHK(hipMalloc(&v1, sizeof(uint32_t) * M));
-    HIPCHK(hipMalloc(&az, sizeof(unsigned) * M));
-    HIPCHK(hipMalloc(&hist, sizeof(unsigned) * (size_t)rs_hist_len(M)));
-    hipLaunchKernelGGL(k_order_keys, dim3(grid_for(M, kBlock)), dim3(kBlock), 0, st, M, M, k0, v0);
-    int which = rt_radix_sort(k0, v0, k1, v1, M, 32, hist, st);
-    if (which) {
-        std::swap(v0, v1);
-        std::swap(k0, k1);
-    }
-    hipLaunchKernelGGL(k_low32, dim3(grid_for(M, kBlock)), dim3(kBlock), 0, st, k0, az, M);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(st));
-    keep = true;
-    cleanup();
-    rt_scene::OrderTable& t = s->otab[s->n_otab++];
-    t.log2m = log2m;
-    t.perm = (int*)v0;
-    t.az = az;
-    s->bytes += sizeof(int) * 2 * M;
-    *out = &t;
-    return RT_OK;
-}
-
-rt_status rt_order_reserve(rt_scene* s, size_t entries, hipStream_t st) {
-    if (s->shifts_cap >= entries) return RT_OK;
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(s->shifts);
-    s->shifts = nullptr;
-    s->shifts_cap = 0;
-    size_t cap = std::max<size_t>(entries, 4096);
-    hipError_t e = hipMalloc(&s->shifts, sizeof(int) * cap);
-    if (e != hipSuccess) return rt_hip_fail(e, "launch order: shift table");
-    s->shifts_cap = cap;
-    return RT_OK;
-}
-
-void rt_order_shifts_single(const rt_scene::OrderTable* t, int64_t N, int* shifts, hipStream_t st) {
-    int64_t chunks = N >> t->log2m;
-    if (chunks <= 0) return;
-    hipLaunchKernelGGL(k_order_shifts, dim3(grid_for(chunks, kBlock), 1), dim3(kBlock), 0, st,
-                       (const TxDesc*)nullptr, N, t->log2m, (const unsigned*)t->az, shifts, chunks);
-}
-
-void rt_order_shifts_multi(const rt_scene::OrderTable* t, const TxDesc* txs, int n_tx, int64_t max_chunks,
-                           int* shifts, hipStream_t st) {
-    if (max_chunks <= 0) return;
-    hipLaunchKernelGGL(k_order_shifts, dim3(grid_for(max_chunks, kBlock), n_tx), dim3(kBlock), 0, st, txs,
-                       (int64_t)0, t->log2m, (const unsigned*)t->az, shifts, max_chunks);
 }
 
 rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t* F, const int32_t* M,
