@@ -368,11 +368,17 @@ rt_status rt_radio_map(const rt_scene* scene, rt_materials materials,
 /*
  * A tape holds, per traced segment, the hit index, the crossed cell, the
  * direction and polarisation basis of the segment and the field transfer
- * matrix T (the per-bounce checkpoint).  Library-owned device memory.
+ * matrix T (the per-bounce checkpoint).  Library-owned device memory, but for
+ * rt_tape_create_in.
  * rt_tape_bytes: bytes a tape for these params needs.
+ * rt_tape_create_in: a tape in device memory of the caller (at least
+ * rt_tape_bytes, 16-byte aligned), which must outlive the tape and the calls
+ * queued on it; destroying the tape frees nothing and does not synchronise.
+ * RT_EINVAL if it is NULL (for a range with rays), misaligned or too small.
  */
 size_t rt_tape_bytes(const rt_sbr_params* params);
 rt_status rt_tape_create(const rt_sbr_params* params, rt_tape** out);
+rt_status rt_tape_create_in(const rt_sbr_params* params, void* memory, size_t bytes, rt_tape** out);
 rt_status rt_tape_destroy(rt_tape* tape);
 
 /*

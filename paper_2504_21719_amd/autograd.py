@@ -16,7 +16,7 @@ import dataclasses
 import torch
 
 from . import rt_build_scene  # noqa: F401  (re-exported for convenience)
-from . import RtScene, make_params, rt_radio_map, rt_radio_map_backward, rt_tape_create
+from . import RtScene, make_params, rt_radio_map, rt_radio_map_backward, tape_from_allocator
 
 
 class RadioMapFn(torch.autograd.Function):
@@ -33,7 +33,8 @@ class RadioMapFn(torch.autograd.Function):
         out = torch.empty((npol, plane.H, plane.W), dtype=torch.float32, device=eps_r.device)
         p = make_params(params)
         need_grad = any(ctx.needs_input_grad[:3])
-        tape = rt_tape_create(p) if need_grad else None
+        # on the current stream, on which the autograd engine also runs the backward
+        tape = tape_from_allocator(p, eps_r.device) if need_grad else None
         diffuse = dict(scattering=scattering, xpd=xpd, scatter_pattern=scatter_pattern)
         rt_radio_map(scene, eps_r.contiguous(), sigma.contiguous(), txo, plane, p, out, tape=tape,
                      thickness=thickness, **diffuse)

@@ -430,11 +430,33 @@ extern "C" rt_status rt_tape_create(const rt_sbr_params* p, rt_tape** out) {
     return RT_OK;
 }
 
+extern "C" rt_status rt_tape_create_in(const rt_sbr_params* p, void* memory, size_t bytes, rt_tape** out) {
+    CHECK_ARG(out != nullptr, "rt_tape_create_in: out is NULL");
+    *out = nullptr;
+    int64_t b, e;
+    rt_status r = check_params(p, &b, &e);
+    if (r != RT_OK) return r;
+    CHECK_ARG(bytes >= rt_tape_bytes(p), "rt_tape_create_in: memory smaller than rt_tape_bytes");
+    CHECK_ARG(memory != nullptr || e == b, "rt_tape_create_in: memory is NULL");
+    CHECK_ARG(((uintptr_t)memory & 15u) == 0, "rt_tape_create_in: memory is not 16-byte aligned");
+    rt_tape* t = new rt_tape();
+    t->n_rays = e - b;
+    t->max_depth = p->max_depth;
+    t->seg = (float4*)memory;
+    t->nseg = (int*)((char*)memory + (size_t)t->n_rays * (size_t)(p->max_depth + 1) * 4 * sizeof(float4));
+    t->bytes = rt_tape_bytes(p);
+    t->owned = false;
+    *out = t;
+    return RT_OK;
+}
+
 extern "C" rt_status rt_tape_destroy(rt_tape* t) {
     if (!t) return RT_OK;
-    (void)hipDeviceSynchronize();
-    (void)hipFree(t->seg);
-    (void)hipFree(t->nseg);
+    if (t->owned) {
+        (void)hipDeviceSynchronize();
+        (void)hipFree(t->seg);
+        (void)hipFree(t->nseg);
+    }
     delete t;
     return RT_OK;
 }

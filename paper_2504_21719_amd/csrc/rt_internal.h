@@ -104,6 +104,7 @@ struct rt_tape {
     float4* seg = nullptr;
     int* nseg = nullptr;
     size_t bytes = 0;
+    bool owned = true;        // seg and nseg are freed with the tape
     // identity of the forward call that filled it
     uint64_t key = 0;
     bool filled = false;
