@@ -56,30 +56,12 @@ extern "C" rt_status rt_build_scene(const float* vertices, int64_t n_vertices, c
     }
     s->n_tri = n_triangles;
     s->n_mat = n_materials;
-    e = hipMalloc(&s->counters, sizeof(unsigned long long) * (RT_QUEUES + 1) * RT_QUEUE_STRIDE);
-    if (e != hipSuccess) {
-        delete s;
-        return rt_hip_fail(e, "hipMalloc(counters)");
-    }
     rt_status r = rt_build_lbvh(s, vertices, n_vertices, triangles, tri_material, st);
     if (r != RT_OK) {
         std::string m = g_err;
         rt_scene_destroy(s);
         return rt_fail(r, m);
     }
-    // traversal spill: (depth + 1 - RT_STACK_LDS) entries for every lane of
-    // the largest persistent grid (a fixed number of lanes per CU)
-    int64_t need_depth = std::max<int64_t>(0, rt_stack_need(s) - RT_STACK_LDS);
-    int64_t lanes = (int64_t)rt_persistent_blocks(64, s->device) * 64;
-    s->spill_entries = (size_t)(need_depth * lanes);
-    if (s->spill_entries) {
-        e = hipMalloc(&s->spill, sizeof(int) * s->spill_entries);
-        if (e != hipSuccess) {
-            rt_scene_destroy(s);
-            return rt_hip_fail(e, "hipMalloc(spill)");
-        }
-    }
-    s->bytes += sizeof(int) * s->spill_entries + sizeof(unsigned long long) * 8;
     *out = s;
     return RT_OK;
 }
@@ -87,13 +69,9 @@ extern "C" rt_status rt_build_scene(const float* vertices, int64_t n_vertices, c
 extern "C" rt_status rt_scene_destroy(rt_scene* s) {
     if (!s) return RT_OK;
     (void)hipDeviceSynchronize();
-    (void)hipFree(s->nodes);
-    (void)hipFree(s->tris);
-    (void)hipFree(s->normals);
-    (void)hipFree(s->wide);
-    (void)hipFree(s->morton);
-    (void)hipFree(s->counters);
-    (void)hipFree(s->spill);
+    (void)hipFree(s->block);
+    (void)hipFree(s->wide_own);
+    (void)hipFree(s->spill_own);
     (void)hipFree(s->tx_desc);
     (void)hipFree(s->grad_ws);
     (void)hipFree(s->geom_ws);

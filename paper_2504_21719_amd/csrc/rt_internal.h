@@ -44,7 +44,11 @@ struct rt_scene {
     int64_t n_tri = 0;
     int32_t n_mat = 0;
     int32_t depth = 0;        // deepest leaf depth (root = 0)
+    int32_t wide_levels = 0;  // levels of the 4-wide tree
     int32_t root = -1;        // child reference of the root (unused if n_tri == 0)
+    void* block = nullptr;    // the scene's memory: all arrays below but the *_own ones
+    void* wide_own = nullptr; // wide nodes, if there are more than the block has room for
+    void* spill_own = nullptr;
     float4* nodes = nullptr;
     float4* tris = nullptr;
     float4* normals = nullptr;
@@ -281,10 +285,12 @@ rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const f
 
 int rt_persistent_blocks(int block, int device);
 
-// Traversal stack entries a query can need: the binary tree pushes at most one
-// entry per level; the wide tree at most three per wide level, and a wide
-// level spans at least one binary level.
-inline int64_t rt_stack_need(const rt_scene* s) { return 3 * (int64_t)s->depth + 2; }
+// Traversal stack entries a query can need: the binary tree defers at most one
+// child per level, the wide tree at most three per wide level.
+inline int64_t rt_stack_need(const rt_scene* s) {
+    const int64_t wide = 3 * (int64_t)s->wide_levels, binary = s->depth;
+    return (wide > binary ? wide : binary) + 2;
+}
 
 // Launch order of `count` consecutive indices of an N-ray lattice
 // (coherent = false: lattice order).
