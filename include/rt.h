@@ -52,7 +52,7 @@
  *     RTMAP_WIDTH (2: binary tree, else 4-wide), RTMAP_ORDER (0: lattice
  *     launch order, else coherent), RTMAP_REFILL (idle lanes a wavefront
  *     waits for before it takes new rays, 1..64), RTMAP_QUEUES (number of
- *     work queues, 1..256), RTMAP_CLAIM (rays per claim, 64..4096),
+ *     work queues, 1..32), RTMAP_CLAIM (rays per claim, 64..4096),
  *     RTMAP_NO_GRAPH (set: rt_radio_map_batched launches its kernels instead
  *     of replaying the captured graph).  They override rt_tune's choice and
  *     rt_set_launch_config.

@@ -583,6 +583,7 @@ extern "C" rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials ma
     bl.n_samples = n_samples;
     bl.n_tx = n_tx;
     bl.total_rays = total;
+    bl.order = hd[0].order;
     bl.total_waves = hw[n_tx];
     fill_plane(plane, params->freq_hz, &bl.pl);
     bl.L = params->max_depth;

@@ -21,11 +21,10 @@
 
 // Empty child slot of a 4-wide node.
 #define RT_WIDE_EMPTY 0x7fffffff
-// Work queues of the persistent kernels: the launch's work indices are split
-// into up to RT_QUEUES contiguous ranges, each with its own counter on its own
-// 256-byte line, so that lane refills do not serialise on one address.  One
-// more line after them counts the queues drained so far.
-#define RT_QUEUES 256
+// Work queues of the persistent kernels: up to RT_QUEUES heads, each on its own
+// 256-byte line, so that refills do not serialise on one address.  One more
+// line after them has a bit per drained queue.
+#define RT_QUEUES 32
 #define RT_QUEUE_STRIDE 32
 
 // LBVH layout.  Internal node = 4 x float4 (64 B, one cache line):
@@ -254,6 +253,7 @@ struct BatchLaunch {
     const float* sigma;
     int32_t n_samples;
     int32_t n_tx;
+    LaunchOrder order;       // of the largest budget
     const TxDesc* tx_dev;    // device [n_tx], ordered largest budget first
     const int64_t* prefix_dev;  // device [n_tx + 1] exclusive prefix of budgets
     const int32_t* tx_slot_dev; // device [n_tx]: output slot of ordered tx
@@ -280,7 +280,7 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st);
 rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const float* sigma, const PlaneDesc& pl,
                                   int L, float t_min, int block, int deposit, int refill,
                                   const TxDesc* txs, const int64_t* prefix, const int32_t* slots, int n_tx,
-                                  int64_t total_rays, bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
+                                  const LaunchOrder& order, int64_t total_rays, bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
                                   float4* geom_seg, int* geom_nseg, const FwdExt* ext, hipStream_t st);
 
 int rt_persistent_blocks(int block, int device);

@@ -464,7 +464,7 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st) {
     const bool grad = b.grad_maps != nullptr;
     if (S == 1 && !grad) {
         return rt_launch_forward_multi(s, b.eps_r, b.sigma, b.pl, b.L, b.t_min, b.block, b.deposit, b.refill,
-                                       b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx, b.total_rays, false, b.maps, HW, HW * b.n_tx, nullptr, nullptr, &b.ext, st);
+                                       b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx, b.order, b.total_rays, false, b.maps, HW, HW * b.n_tx, nullptr, nullptr, &b.ext, st);
     }
     size_t need = sizeof(float4) * 2 * (size_t)(b.L + 1) * (size_t)b.total_rays + sizeof(int) * (size_t)b.total_rays;
     const int P = 2 * s->n_mat + 3;
@@ -473,7 +473,7 @@ rt_status rt_launch_batched(const BatchLaunch& b, hipStream_t st) {
     float4* geom = (float4*)s->geom_ws;
     int* nseg = (int*)((char*)s->geom_ws + sizeof(float4) * 2 * (size_t)(b.L + 1) * (size_t)b.total_rays);
     rt_status r = rt_launch_forward_multi(s, b.eps_r, b.sigma, b.pl, b.L, b.t_min, b.block, b.deposit, b.refill,
-                                          b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx, b.total_rays, true, b.maps, HW, HW * b.n_tx * S, geom, nseg, nullptr, st);
+                                          b.tx_dev, b.prefix_dev, b.tx_slot_dev, b.n_tx, b.order, b.total_rays, true, b.maps, HW, HW * b.n_tx * S, geom, nseg, nullptr, st);
     if (r != RT_OK) return r;
     SampArgs a;
     a.geom = geom;

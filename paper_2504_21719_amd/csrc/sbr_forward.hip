@@ -3,9 +3,7 @@
 // One lane carries one ray at a time.  A lane whose ray has ended takes the
 // next lattice index from a device work queue (one atomic per wavefront,
 // shared out with ballot/mbcnt), so wavefronts stay full while ray lengths
-// differ.  The work indices are split into contiguous queues with separate
-// counters; a wavefront starts on its own queue and moves on to the next once
-// that is drained, until it has found every queue drained.  Per traced segment l the lane
+// differ (queue_entry says what a claim holds).  Per traced segment l the lane
 //   1. finds the closest hit through the LBVH, the wavefront's lanes together
 //      while they want the same nodes, else each on its own (short LDS stack,
 //      spill to a per-lane global area sized from the tree depth), or by
@@ -65,11 +63,17 @@ struct FwdArgs {
     int32_t* cells;
     float* weights;
     unsigned long long* stats;
-    unsigned long long* counter;   // RT_QUEUES heads, RT_QUEUE_STRIDE apart
+    // work queues (see queue_entry)
+    unsigned long long* counter;   // RT_QUEUES heads, then the mask of drained queues, RT_QUEUE_STRIDE apart
+    unsigned long long per_queue;  // entries per queue
+    int64_t n_units;               // units of `claim` indices (`once`: of `width`)
+    int64_t mid;                   // unit that comes first, -1 = in ascending order
     int nq;                        // queues in use (1..RT_QUEUES)
-    int qrem;                      // queues q < qrem hold qper + 1 work indices, the others qper
-    unsigned long long qper;
-    int claim;                     // work indices claimed per queue atomic (>= 64)
+    int once;                      // 1: every wavefront has at most one unit, its own
+    int width;                     // rays a wavefront starts at once, on its first lanes
+    int claim;                     // work indices per unit
+    unsigned n_claim;              // entries of a queue that are such units; the rest are of `width`
+    unsigned run, n_run;           // consecutive units per queue turn, among the first n_run entries
     // early termination (kernel variant EXT): before segments l >= rr_depth
     int rr_depth;
     float rr_p_max;                // Russian roulette, 0 = off
@@ -115,6 +119,52 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
         else hi = mid;
     }
     return lo;
+}
+
+// Work of entry i of queue q: indices [*first, *end), possibly none.
+//
+// The grid is what is resident (four wavefronts per SIMD); each wavefront
+// starts with the entry of its number and claims the next from its queue's
+// head with one atomic.  A wavefront of near-horizontal rays takes 0.13 ms in
+// the city and 0.3 ms and more on the 1.02 M-triangle scene, as long as
+// hundreds of others, so what counts in a call of few units per wavefront is
+// that those start first: the units of one transmitter follow outward from the
+// lattice's equator, above and below in turn, and straight-down and
+// straight-up rays, the shortest, make the tail.  All wavefronts advance along
+// one front, cut over the queues by unit, so that no queue is drained much
+// before another (contiguous ranges per queue leave the horizon's range to the
+// end); `run` units in a row go to one queue, whose workgroups share an XCD's
+// L2, about a quarter of the front's turn in all.  Several transmitters come
+// largest budget first, in lattice order, and change to units of one wavefront
+// for the last 32 per wavefront.
+//
+// City map, 2e6 rays: 304 -> 164 us, 1e6 225 -> 155, 4e6 455 -> 287, 3e7 1.79
+// -> 1.77 ms; 1.02 M triangles, 1e6 627 -> 550 us, 4e6 977 -> 692, 6.4e7 6.9 ->
+// 6.8 ms; 64 rooftop transmitters of up to 1e7 rays 6.65 -> 6.3 ms, against
+// contiguous ranges on up to 256 queues with two grids' worth of workgroups.
+// Units of four wavefronts already at the horizon cost 0.45 ms more there.
+__device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
+    *first = *end = 0;
+    if (i < a.n_claim) {
+        int64_t u = (int64_t)i * a.nq + q;
+        if (i < a.n_run) {
+            const unsigned r = i / a.run;
+            u = ((int64_t)r * a.nq + q) * a.run + (i - r * a.run);
+        }
+        if (u >= a.n_units) return;
+        if (a.mid >= 0) {
+            // outward from mid: the two sides in turn, then the rest of the longer one
+            const int64_t above = a.n_units - a.mid, both = 2 * min(a.mid, above), v = u >> 1;
+            u = u < both ? ((u & 1) ? a.mid + v : a.mid - 1 - v) : (a.mid > above ? a.n_units - 1 - u : u);
+        }
+        *first = u * a.claim;
+        *end = min(a.n_work, *first + a.claim);
+    } else {
+        const int64_t f = (int64_t)a.n_claim * a.nq * a.claim + ((int64_t)(i - a.n_claim) * a.nq + q) * a.width;
+        if (f >= a.n_work) return;
+        *first = f;
+        *end = min(a.n_work, f + a.width);
+    }
 }
 
 // A wavefront leaves the common walk once the visits that few lanes wanted add
@@ -587,10 +637,28 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
 
     bool active = false;
     bool exhausted = false;
-    // this wavefront's first queue (held in scalar registers)
-    int q = uniform((int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % (unsigned)kernel_args().nq));
-    int drained = 0;                   // queues found drained so far
-    unsigned long long res_b = 0, res_e = 0;                         // claimed, not yet started
+    // this wavefront's queue (a workgroup's wavefronts share one, and so do the
+    // workgroups that share an XCD) and first entry
+    int q = 0;
+    int looks = 0;                     // at the mask of drained queues
+    int64_t res_b = 0, res_e = 0;      // claimed work indices, not yet started
+    {
+        const FwdArgs& a = kernel_args();
+        const unsigned w = (unsigned)uniform((int)(threadIdx.x >> 6)), per_block = blockDim.x >> 6;
+        exhausted = a.once != 0;
+        if (a.once) {
+            // neighbouring wavefronts from eight stretches of the order, so that the
+            // long ones do not share a CU
+            const int64_t each = (a.n_units + 7) >> 3, wave = (int64_t)blockIdx.x * per_block + w;
+            if ((wave >> 3) < each) {
+                res_b = min(a.n_work, ((wave & 7) * each + (wave >> 3)) * a.width);
+                res_e = min(a.n_work, res_b + a.width);
+            }
+        } else {
+            q = (int)(blockIdx.x % (unsigned)a.nq);
+            queue_entry(a, blockIdx.x / (unsigned)a.nq * per_block + w, q, &res_b, &res_e);
+        }
+    }
     int64_t rid = 0;          // ray index relative to ray_begin
     int l = 0;
     int last = -1;
@@ -608,59 +676,53 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
 
     while (true) {
         // ---- refill lanes without a ray: from this wavefront's reservoir of
-        // claimed work indices, claiming a new batch from the queues when the
-        // reservoir cannot cover every idle lane
+        // claimed work indices, claiming more when it cannot cover every idle
+        // lane
         if (!exhausted || res_b < res_e) {
             const FwdArgs& a = kernel_args();
-            unsigned long long need = __ballot(!active);
-            if (need && (__popcll(need) >= a.refill || need == ~0ull)) {
+            const unsigned long long own = ~0ull >> (64 - a.width);
+            const unsigned long long need = __ballot(!active) & own;
+            if (need && (__popcll(need) >= a.refill || need == own)) {
                 const unsigned cnt = (unsigned)__popcll(need);
                 // wave-uniform: every value below is the same on all lanes
-                unsigned long long b1 = res_b, e1 = res_e, b2 = 0, e2 = 0;
-                if (e1 - b1 < cnt && !exhausted) {
-                    const unsigned long long claim = (unsigned long long)a.claim;   // work indices per atomic
-                    while (true) {
-                        // queue q holds work indices [qb, qe): per or per + 1 of them
-                        const unsigned long long qb = (unsigned long long)q * a.qper + (unsigned)min(q, a.qrem);
-                        const unsigned long long qn = a.qper + (q < a.qrem ? 1ull : 0ull);
-                        unsigned long long b = 0;
-                        if (lane == 0) b = atomicAdd(a.counter + q * RT_QUEUE_STRIDE, claim);
-                        b = uniform_u64(b);
-                        const bool got = b < qn;
-                        if (got) {
-                            b2 = qb + b;
-                            e2 = qb + min(qn, b + claim);
-                        }
-                        if (got && b + claim >= qn) {
-                            // this claim drained queue q (exactly one claim per queue does)
-                            if (lane == 0) atomicAdd(a.counter + RT_QUEUES * RT_QUEUE_STRIDE, 1ull);
-                        }
-                        if (!got) {
-                            // drained earlier: stop once every queue is, else try the next
-                            unsigned long long nd = 0;
-                            if (lane == 0)
-                                nd = __hip_atomic_load(a.counter + RT_QUEUES * RT_QUEUE_STRIDE, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-                            nd = uniform_u64(nd);
-                            if (nd >= (unsigned long long)a.nq || ++drained >= a.nq) exhausted = true;
-                        }
-                        if (!got || b + claim >= qn) q = q + 1 == a.nq ? 0 : q + 1;
-                        if (got || exhausted) break;
+                const int64_t b1 = res_b, e1 = res_e;
+                int64_t b2 = 0, e2 = 0;
+                while (e1 - b1 < (int64_t)cnt && b2 == e2 && !exhausted) {
+                    unsigned long long i = 0;
+                    if (lane == 0) i = atomicAdd(a.counter + q * RT_QUEUE_STRIDE, 1ull);
+                    i = uniform_u64(i);
+                    if (i < a.per_queue) {
+                        // the last entry of a queue (one claim per queue) marks it
+                        if (i + 1 == a.per_queue && lane == 0)
+                            atomicOr(a.counter + RT_QUEUES * RT_QUEUE_STRIDE, 1ull << q);
+                        queue_entry(a, (unsigned)i, q, &b2, &e2);
+                    } else {
+                        // drained: on to the next queue that is not marked
+                        unsigned long long m = 0;
+                        if (lane == 0)
+                            m = __hip_atomic_load(a.counter + RT_QUEUES * RT_QUEUE_STRIDE, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+                        m = ~uniform_u64(m) & ((1ull << a.nq) - 1ull) & ~(1ull << q);
+                        // a bound on the looks: every queue is emptied by its own
+                        // wavefronts, so leaving early loses nothing
+                        exhausted = m == 0ull || ++looks > 2 * RT_QUEUES;
+                        const unsigned long long up = m >> q << q;
+                        if (m) q = __builtin_ctzll(up ? up : m);
                     }
                 }
                 // idle lanes take the reservoir first, then the new batch
-                const unsigned long long n1 = e1 - b1;
-                const unsigned long long take1 = min((unsigned long long)cnt, n1);
-                const unsigned long long take2 = min((unsigned long long)cnt - take1, e2 - b2);
+                const int64_t n1 = e1 - b1;
+                const int64_t take1 = min((int64_t)cnt, n1);
+                const int64_t take2 = min((int64_t)cnt - take1, e2 - b2);
                 res_b = take1 < n1 ? b1 + take1 : b2 + take2;
                 res_e = take1 < n1 ? e1 : e2;
-                if (!active) {
+                if (!active && lane < a.width) {
                     const unsigned rank = __builtin_amdgcn_mbcnt_hi((unsigned)(need >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((unsigned)need, 0u));
                     const bool mine = rank < (unsigned)(take1 + take2);
-                    const unsigned long long my = rank < (unsigned)take1 ? b1 + rank : b2 + (rank - (unsigned)take1);
+                    const int64_t my = rank < (unsigned)take1 ? b1 + rank : b2 + (rank - (unsigned)take1);
                     if (mine) {
-                        rid = (int64_t)my;
+                        rid = my;
                         int64_t n;
                         const TxDesc* tp;
                         if (MODE == MODE_SINGLE) {
@@ -958,13 +1020,21 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
     }
 }
 
-// Zero the map (unless accumulating) and reset the work-queue heads and the
-// drained count (launched with at least two 256-thread blocks, so that the
-// grid has more than RT_QUEUES threads).  A kernel,
-// not a memset, so that the whole call can be captured in a HIP graph.
-__global__ void k_prepare(float* __restrict__ map, int64_t n, unsigned long long* __restrict__ counter) {
+// Zero the map (unless accumulating), set the heads of the work queues behind
+// the wavefronts' first entries and mark the queues that these drain (launched
+// with at least two 256-thread blocks, so that the grid has more than RT_QUEUES
+// threads).  A kernel, not a memset, so that the whole call can be captured in
+// a HIP graph.
+__global__ void k_prepare(float* __restrict__ map, int64_t n, unsigned long long* __restrict__ counter, int nq,
+                          unsigned long long per_queue, int blocks, int waves_per_block) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i <= RT_QUEUES) counter[i * RT_QUEUE_STRIDE] = 0ull;
+    auto head = [&](int q) { return (unsigned long long)((blocks - q + nq - 1) / nq) * (unsigned)waves_per_block; };
+    if (i < nq) counter[i * RT_QUEUE_STRIDE] = head((int)i);
+    if (i == RT_QUEUES) {
+        unsigned long long drained = 0;
+        for (int q = 0; q < nq; q++) drained |= head(q) >= per_queue ? 1ull << q : 0ull;
+        counter[i * RT_QUEUE_STRIDE] = drained;
+    }
     for (; i < n; i += (int64_t)gridDim.x * blockDim.x) map[i] = 0.0f;
 }
 
@@ -1009,8 +1079,9 @@ int rt_persistent_blocks(int block, int device) {
         if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || c <= 0) c = 256;
         cu[dev] = c;
     }
-    // enough resident waves per CU to hide traversal latency
-    int waves_per_cu = 32;
+    // what is resident: four wavefronts per SIMD (registers; 16 of a CU's stacks
+    // take 128 KB of LDS)
+    int waves_per_cu = 16;
     int blocks_per_cu = std::max(1, waves_per_cu * 64 / block);
     return cu[dev] * blocks_per_cu;
 }
@@ -1037,39 +1108,66 @@ static void base_args(FwdArgs& a, const rt_scene* s, int block, const float* eps
     a.refill = 1;
 }
 
-static rt_status size_spill(FwdArgs& a, const rt_scene* s, int block, int* blocks_out) {
-    // persistent grid, but no more workgroups than give each lane about four rays
-    int blocks = rt_persistent_blocks(block, s->device);
-    blocks = (int)std::min<int64_t>(blocks, std::max<int64_t>(256, (a.n_work + 4LL * block - 1) / (4LL * block)));
-    int64_t threads = (int64_t)blocks * block;
+// Grid, work queues and spill area of one launch of a.n_work rays.
+static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const LaunchOrder& order, int* blocks_out) {
+    const int per_block = block / 64;
+    int64_t blocks = rt_persistent_blocks(block, s->device);
+    int64_t waves = blocks * per_block;
+    // fewer rays than the resident wavefronts have lanes: narrower wavefronts
+    // (whose lanes wait less for each other), at least 8 rays wide
+    a.width = 64;
+    while (a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
+    a.n_units = (a.n_work + a.width - 1) / a.width;
+    a.once = (a.n_units + 7) / 8 * 8 <= waves;
+    a.mid = -1;
+    a.nq = 1;
+    a.run = 1;
+    a.claim = a.width;
+    if (a.once) {
+        blocks = std::max<int64_t>(1, ((a.n_units + 7) / 8 * 8 + per_block - 1) / per_block);
+    } else {
+        // claims on one head follow each other at 25 ns, 16 heads keep up with the
+        // shortest rays (14 triangles, 3e6 rays: 124 us with 8, 101 us with 16);
+        // more heads cost the wavefronts more looks at the end
+        a.nq = 16;
+        if (const char* env = getenv("RTMAP_QUEUES"))
+            a.nq = std::max(1, std::min(RT_QUEUES, atoi(env)));
+        a.nq = (int)std::min<int64_t>(a.nq, blocks);
+        // units small enough that every wavefront runs about 16 of them, large
+        // enough to keep queue atomics rare; whole multiples of the wavefront,
+        // so that a refill stays on one stretch of the launch order
+        a.claim = 64 * (int)std::max<int64_t>(1, std::min<int64_t>(4, a.n_units / (waves * 16)));
+        if (const char* env = getenv("RTMAP_CLAIM"))
+            a.claim = std::max(64, std::min(4096, atoi(env)));
+        const int64_t narrow = a.n_tx > 1 ? 32 * waves * a.width : 0;     // indices left to units of one wavefront
+        if (a.n_tx > 1) {
+            a.n_units = std::max<int64_t>(0, a.n_work - narrow) / a.claim / a.nq * a.nq;
+        } else {
+            a.n_units = (a.n_work + a.claim - 1) / a.claim;
+            const int64_t equator = a.n_tx == 1 ? a.n_work / 2 : a.tx.n_rays / 2 - a.ray_begin;
+            a.mid = std::min(a.n_units, std::max<int64_t>(0, equator / a.claim));
+            a.run = (unsigned)std::max<int64_t>(1, rt_order_chunk(order) / (2 * a.claim * a.nq));
+        }
+    }
+    a.n_claim = (unsigned)((a.n_units + a.nq - 1) / a.nq);
+    // whole turns of every queue, so that the rest is a stretch of its own
+    a.n_run = (unsigned)(a.n_units / ((int64_t)a.run * a.nq)) * a.run;
+    const int64_t rest = std::max<int64_t>(0, a.n_work - (int64_t)a.n_claim * a.nq * a.claim);
+    a.per_queue = a.n_claim + (unsigned long long)((rest + (int64_t)a.width * a.nq - 1) / ((int64_t)a.width * a.nq));
+    const int64_t threads = blocks * block;
     // a wide traversal pushes up to 3 entries per wide level (= 2 binary levels)
     int64_t need_depth = std::max<int64_t>(0, rt_stack_need(s) - RT_STACK_LDS);
     if ((int64_t)s->spill_entries < need_depth * threads)
         return rt_fail(RT_EOVERFLOW, "traversal spill area too small for this launch");
     a.spill_stride = threads;
     a.spill_depth = (int)need_depth;
-    *blocks_out = blocks;
+    *blocks_out = (int)blocks;
     return RT_OK;
 }
 
 template <int MODE>
-static void launch_mode(const FwdArgs& args, int accel, bool wide, int blocks, int block, hipStream_t st,
+static void launch_mode(const FwdArgs& a, int accel, bool wide, int blocks, int block, hipStream_t st,
                         bool ext = false) {
-    FwdArgs a = args;
-    // about 4096 work items per queue, at most RT_QUEUES queues
-    a.nq = (int)std::max<int64_t>(1, std::min<int64_t>(RT_QUEUES, a.n_work / 4096));
-    if (const char* env = getenv("RTMAP_QUEUES"))
-        a.nq = std::max(1, std::min(RT_QUEUES, atoi(env)));
-    a.qper = (unsigned long long)a.n_work / (unsigned long long)a.nq;
-    a.qrem = (int)((unsigned long long)a.n_work % (unsigned long long)a.nq);
-    // claims small enough that every wavefront makes about 16 of them (a
-    // wavefront runs its claimed rays one after another, so large claims
-    // lengthen the tail), large enough to keep queue atomics rare; whole
-    // multiples of the wavefront, so that a refill stays on one stretch of the
-    // launch order
-    a.claim = 64 * (int)std::max<int64_t>(1, std::min<int64_t>(4, a.n_work / ((int64_t)blocks * block * 16)));
-    if (const char* env = getenv("RTMAP_CLAIM"))
-        a.claim = std::max(64, std::min(4096, atoi(env)));
     const size_t lds = sizeof(int2) * RT_STACK_LDS * block;   // {node, entry distance} per entry
     // calls with records, statistics or a tape, and the extensions, carry the
     // transfer matrix; the others the fields themselves
@@ -1132,13 +1230,14 @@ rt_status rt_launch_forward(const FwdLaunch& f, hipStream_t st) {
     a.stats = f.stats;
     a.refill = std::max(1, std::min(64, f.refill));
     int blocks = 0;
-    rt_status r = size_spill(a, s, f.block, &blocks);
+    rt_status r = size_launch(a, s, f.block, f.tx.order, &blocks);
     if (r != RT_OK) return r;
     int64_t map_n = a.map_stride * a.npol;
     {
         int64_t zn = f.zero_map ? map_n : 0;
         int g = (int)std::min<int64_t>(2048, std::max<int64_t>(2, (zn + 255) / 256));
-        hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, f.map, zn, s->counters);
+        hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, f.map, zn, s->counters, a.nq,
+                           a.per_queue, blocks, f.block / 64);
     }
     a.rr_depth = f.rr_depth;
     a.rr_p_max = f.rr_p_max;
@@ -1165,7 +1264,7 @@ rt_status rt_launch_forward(const FwdLaunch& f, hipStream_t st) {
 rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const float* sigma, const PlaneDesc& pl,
                                   int L, float t_min, int block, int deposit, int refill,
                                   const TxDesc* txs, const int64_t* prefix, const int32_t* slots, int n_tx,
-                                  int64_t total_rays, bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
+                                  const LaunchOrder& order, int64_t total_rays, bool geom_only, float* maps, int64_t slot_stride, int64_t zero_floats,
                                   float4* geom_seg, int* geom_nseg, const FwdExt* ext, hipStream_t st) {
     FwdArgs a;
     base_args(a, s, block, eps_r, sigma, pl, L, t_min);
@@ -1187,10 +1286,11 @@ rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const f
         a.tape_groups = 2;
     }
     int blocks = 0;
-    rt_status r = size_spill(a, s, block, &blocks);
+    rt_status r = size_launch(a, s, block, order, &blocks);
     if (r != RT_OK) return r;
     int g = (int)std::min<int64_t>(4096, std::max<int64_t>(2, (zero_floats + 255) / 256));
-    hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, maps, zero_floats, s->counters);
+    hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, maps, zero_floats, s->counters, a.nq,
+                       a.per_queue, blocks, block / 64);
     bool use_ext = false;
     if (ext && !geom_only) {
         a.rr_depth = ext->rr_depth;
