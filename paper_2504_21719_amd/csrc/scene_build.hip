@@ -16,8 +16,9 @@
 //               from longest-common-prefix lengths (Karras, HPG 2012) and the
 //               boxes of its two children, which are runs of consecutive
 //               triangles, from the box levels
-//   4-wide      the wide nodes are found level by level from the root (lists),
-//               numbered by a scan and written
+//   splits      few triangles: a second binary tree, split by surface area
+//   4-wide      the wide nodes are found level by level from the root (lists) of
+//               that or of the hierarchy, numbered by a scan and written
 // An invalid mesh runs through all of it with a stand-in point for what cannot
 // be read, so that the flags need no read-back of their own.
 //
@@ -30,6 +31,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstddef>
 #include <cstring>
@@ -75,6 +77,7 @@ struct BuildState {
     unsigned err;                      // 1 vertex index, 2 material id, 4 non-finite coordinate
     int max_depth;                     // deepest leaf
     unsigned n_wide;
+    int n_small;                       // subtrees that k_sah_top left
     int next_level;                    // first level that k_wide_top left
     int count[kMaxLevels + 1];         // wide nodes per level
     unsigned totals[8][256];           // digit counts of the sort's passes
@@ -202,6 +205,43 @@ __global__ void __launch_bounds__(kBlock) k_morton(const float* __restrict__ V, 
     for (int d = 0; d < 8; d++) {
         const unsigned c = h[d][threadIdx.x];
         if (c) atomicAdd(&st->totals[d][threadIdx.x], c);
+    }
+}
+
+// ---- sort of few triangles --------------------------------------------------
+// One workgroup sorts up to kSortOne pairs in LDS by (code, triangle), a bitonic
+// network: the radix sort's 24 launches take 116 us at any small size, this
+// takes 28 us for the 1202 triangles of the city.
+constexpr int kSortOne = 2048, kSortBlock = 1024;
+__global__ void __launch_bounds__(kSortBlock) k_sort_one(uint64_t* __restrict__ keys, uint32_t* __restrict__ vals, int n) {
+    __shared__ uint64_t k[kSortOne];
+    __shared__ uint32_t v[kSortOne];
+    int size = 2;
+    while (size < n) size *= 2;
+    for (int i = threadIdx.x; i < size; i += kSortBlock) {
+        k[i] = i < n ? keys[i] : ~0ull;
+        v[i] = i < n ? vals[i] : 0xffffffffu;
+    }
+    __syncthreads();
+    for (int run = 2; run <= size; run *= 2)
+        for (int step = run / 2; step > 0; step /= 2) {
+            for (int t = threadIdx.x; t < size / 2; t += kSortBlock) {
+                const int i = 2 * t - (t & (step - 1)), j = i + step;
+                const uint64_t a = k[i], b = k[j];
+                const uint32_t x = v[i], y = v[j];
+                const bool after = a > b || (a == b && x > y);
+                if (after == ((i & run) == 0)) {
+                    k[i] = b;
+                    k[j] = a;
+                    v[i] = y;
+                    v[j] = x;
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = threadIdx.x; i < n; i += kSortBlock) {
+        keys[i] = k[i];
+        vals[i] = v[i];
     }
 }
 
@@ -600,6 +640,366 @@ __device__ __forceinline__ int wide_children(const float4* __restrict__ nodes, i
     return cnt;
 }
 
+// ---- small scenes: a tree of least surface area ----------------------------
+// Up to kSahMax triangles, the wide nodes are taken from a second binary tree,
+// split top-down at the least expected cost (surface area times triangles on
+// both sides, MacDonald and Booth 1990).  Codes put a triangle where its centre
+// is, so that one as large as the scene (a ground plane) widens every box down
+// to a single house's: on the city (1202 triangles, ground of 2) a segment
+// visits 7.5 wide nodes of the Karras tree and 5.0 of this one.  Maps of 1e6 and
+// 1e7 rays 162 -> 135 and 618 -> 539 us, 64 rooftop transmitters 6.3 -> 5.3 ms;
+// the build 306 -> 435 us, of which k_sah_top 137 and k_sah_small 86 us (serial:
+// one wavefront per node and level).  Larger scenes are left out because one
+// workgroup makes the upper splits (at 4096 triangles it takes what a map of
+// 1e6 rays gains, at 8192 twice that), and for what it would give them: 9 % of the
+// visits on the 1.02 M-triangle terrain, whose triangles are alike.
+//
+// Node numbers are those of a depth-first walk: the left child of node i is
+// i + 1, the right one i + (leaves on the left); triangle order within a node
+// is kept by every split.  So the tree does not depend on the order in which
+// its parts are made.
+constexpr int kSahMax = 4096;
+constexpr int kSahBins = 16, kSahSmall = 64;
+constexpr int kSahBlock = 1024, kSahWaves = kSahBlock / 64;
+constexpr int kSahDeep = 32;               // at this depth and below, halves
+constexpr int kSahQueue = kSahMax / kSahSmall;
+
+__device__ __forceinline__ void wave_fence() {
+    __threadfence_block();
+    __builtin_amdgcn_wave_barrier();
+}
+// These two round the same wherever they are inlined (no contraction): a count
+// and the partition that it sizes must agree.
+__device__ __forceinline__ float box_centre(const Box& b, int a) {
+#pragma clang fp contract(off)
+    return 0.5f * b.lo[a] + 0.5f * b.hi[a];
+}
+__device__ __forceinline__ int sah_bin(float centre, float lo, float scale) {
+#pragma clang fp contract(off)
+    return (int)fminf((centre - lo) * scale, (float)(kSahBins - 1));
+}
+__device__ __forceinline__ void box_add_if(Box& to, const Box& b, bool on) {
+    for (int x = 0; x < 3; x++) {
+        to.lo[x] = fminf(to.lo[x], on ? b.lo[x] : INFINITY);
+        to.hi[x] = fmaxf(to.hi[x], on ? b.hi[x] : -INFINITY);
+    }
+}
+// A triangle's box with its slot, as box_store writes it but for the slot.
+struct SahBox {
+    Box box;
+    int id;
+};
+__device__ __forceinline__ SahBox sah_load(const float4* __restrict__ p, int i) {
+    const float4 u = p[2 * i], v = p[2 * i + 1];
+    return SahBox{{{u.x, u.y, u.z}, {u.w, v.x, v.y}}, __float_as_int(v.z)};
+}
+__device__ __forceinline__ void sah_store(float4* __restrict__ p, int i, const SahBox& b) {
+    p[2 * i] = make_float4(b.box.lo[0], b.box.lo[1], b.box.lo[2], b.box.hi[0]);
+    p[2 * i + 1] = make_float4(b.box.hi[1], b.box.hi[2], __int_as_float(b.id), 0.0f);
+}
+// Four loads in flight: f(box, index, index < end) for the wavefront's indices
+// lo + lane, in order.
+template <typename F>
+__device__ __forceinline__ void sah_for(const float4* __restrict__ p, int lo, int end, int lane, F f) {
+    for (int i = lo + lane; i - lane < end; i += 256) {
+        SahBox b[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) b[k] = sah_load(p, min(i + 64 * k, end - 1));
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if (i - lane + 64 * k < end) f(b[k], i + 64 * k, i + 64 * k < end);
+    }
+}
+// FLT_MAX at most, so that an overflow still orders; no box: 0
+__device__ __forceinline__ float split_cost(const Box& l, int nl, const Box& r, int nr) {
+    return fminf(box_area(l.lo, l.hi) * (float)nl + box_area(r.lo, r.hi) * (float)nr, FLT_MAX);
+}
+__device__ __forceinline__ void node_store(float4* __restrict__ nodes, int i, const Box& L, const Box& R, int left,
+                                           int right) {
+    nodes[4 * (int64_t)i + 0] = make_float4(L.lo[0], L.hi[0], L.lo[1], L.hi[1]);
+    nodes[4 * (int64_t)i + 1] = make_float4(R.lo[0], R.hi[0], R.lo[1], R.hi[1]);
+    nodes[4 * (int64_t)i + 2] = make_float4(L.lo[2], L.hi[2], R.lo[2], R.hi[2]);
+    nodes[4 * (int64_t)i + 3] = make_float4(__int_as_float(left), __int_as_float(right), 0.0f, 0.0f);
+}
+
+// Splits every node of more than kSahSmall triangles, level by level, one
+// wavefront per node: bounds of the centres, kSahBins bins per axis, the best
+// of the 3 (kSahBins - 1) planes (one per lane), a stable partition.  A task is
+// {first, end, node, -}; those left for k_sah_small are {first, end, node, which
+// of the two buffers}.  At the end, the depth of the Karras tree `karras`,
+// by doubling the parent links.
+__global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict__ boxes, int n,
+                                                       const float4* __restrict__ karras, float4* __restrict__ nodes,
+                                                       float4* buf0, float4* buf1, int4* __restrict__ small,
+                                                       BuildState* __restrict__ st) {
+    __shared__ unsigned bins[kSahWaves][3][kSahBins][7];     // ordered-int lo, hi; count
+    __shared__ int4 list[2][kSahQueue];
+    __shared__ int count[2], n_small;
+    __shared__ unsigned short par[kSahMax], dep[kSahMax];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < n; i += kSahBlock) {
+        SahBox b = sah_load(boxes, i);
+        b.id = i;
+        sah_store(buf0, i, b);
+    }
+    if (threadIdx.x == 0) {
+        n_small = n <= kSahSmall ? 1 : 0;
+        count[0] = 1 - n_small;
+        count[1] = 0;
+        if (n_small) small[0] = make_int4(0, n, 0, 0);
+        else list[0][0] = make_int4(0, n, 0, 0);
+    }
+    __syncthreads();
+    for (int level = 0; count[level & 1] > 0; level++) {
+        const float4* in = level & 1 ? buf1 : buf0;
+        float4* out = level & 1 ? buf0 : buf1;
+        for (int t = wave; t < count[level & 1]; t += kSahWaves) {
+            const int4 task = list[level & 1][t];
+            const int lo = task.x, hi = task.y, cnt = hi - lo;
+            unsigned(*const bn)[kSahBins][7] = bins[wave];
+            Box c = kNoBox;
+            sah_for(in, lo, hi, lane, [&](const SahBox& b, int, bool) {      // the last one again is no harm
+                for (int a = 0; a < 3; a++) {
+                    c.lo[a] = fminf(c.lo[a], box_centre(b.box, a));
+                    c.hi[a] = fmaxf(c.hi[a], box_centre(b.box, a));
+                }
+            });
+            float scale[3];
+            for (int a = 0; a < 3; a++) {
+                for (int off = 32; off >= 1; off >>= 1) {
+                    c.lo[a] = fminf(c.lo[a], __shfl_xor(c.lo[a], off));
+                    c.hi[a] = fmaxf(c.hi[a], __shfl_xor(c.hi[a], off));
+                }
+                const float ext = c.hi[a] - c.lo[a];
+                scale[a] = ext > 0.0f ? (float)kSahBins / ext : 0.0f;
+            }
+            auto bin = [&](const Box& b, int a) { return sah_bin(box_centre(b, a), c.lo[a], scale[a]); };
+            for (int i = lane; i < 3 * kSahBins * 7; i += 64) (&bn[0][0][0])[i] = i % 7 < 3 ? 0xffffffffu : 0u;
+            wave_fence();
+            sah_for(in, lo, hi, lane, [&](const SahBox& b, int, bool on) {
+                if (!on) return;
+                for (int a = 0; a < 3; a++) {
+                    unsigned* const w = bn[a][bin(b.box, a)];
+                    for (int x = 0; x < 3; x++) {
+                        atomicMin(w + x, f2ord(b.box.lo[x]));
+                        atomicMax(w + 3 + x, f2ord(b.box.hi[x]));
+                    }
+                    atomicAdd(w + 6, 1u);
+                }
+            });
+            wave_fence();
+            // lane = axis (kSahBins - 1) + plane
+            const int axis = lane < kSahBins - 1 ? 0 : lane < 2 * (kSahBins - 1) ? 1 : 2;
+            const int plane = lane - axis * (kSahBins - 1) + 1;
+            Box L = kNoBox, R = kNoBox;
+            int nl = 0, nr = 0;
+            for (int k = 0; k < kSahBins; k++) {
+                const unsigned* const w = bn[axis][k];
+                if (w[6] == 0u) continue;
+                Box b;
+                for (int x = 0; x < 3; x++) {
+                    b.lo[x] = ord2f(w[x]);
+                    b.hi[x] = ord2f(w[3 + x]);
+                }
+                box_add_if(L, b, k < plane);
+                box_add_if(R, b, k >= plane);
+                nl += k < plane ? (int)w[6] : 0;
+                nr += k < plane ? 0 : (int)w[6];
+            }
+            float cost = plane < kSahBins && nl > 0 && nr > 0 ? split_cost(L, nl, R, nr) : INFINITY;
+            int best = lane;
+            for (int off = 32; off >= 1; off >>= 1) {
+                const float c2 = __shfl_xor(cost, off);
+                const int b2 = __shfl_xor(best, off);
+                if (c2 < cost || (c2 == cost && b2 < best)) {
+                    cost = c2;
+                    best = b2;
+                }
+            }
+            const bool halves = !(cost < INFINITY) || level >= kSahDeep;
+            const int ax = __shfl(axis, best), pl = __shfl(plane, best);
+            const int n_left = halves ? cnt / 2 : __shfl(nl, best);
+            L = R = kNoBox;
+            int done_l = 0, done_r = 0;
+            sah_for(in, lo, hi, lane, [&](const SahBox& b, int i, bool on) {
+                const int side = ax == 0 ? bin(b.box, 0) : ax == 1 ? bin(b.box, 1) : bin(b.box, 2);
+                const bool left = on && (halves ? i < lo + n_left : side < pl);
+                const unsigned long long ml = __ballot(left), mr = __ballot(on && !left);
+                const unsigned long long below = (1ull << lane) - 1ull;
+                box_add_if(L, b.box, left);
+                box_add_if(R, b.box, on && !left);
+                if (on)
+                    sah_store(out, left ? lo + done_l + (int)__popcll(ml & below)
+                                        : lo + n_left + done_r + (int)__popcll(mr & below), b);
+                done_l += (int)__popcll(ml);
+                done_r += (int)__popcll(mr);
+            });
+            for (int x = 0; x < 3; x++)
+                for (int off = 32; off >= 1; off >>= 1) {
+                    L.lo[x] = fminf(L.lo[x], __shfl_xor(L.lo[x], off));
+                    L.hi[x] = fmaxf(L.hi[x], __shfl_xor(L.hi[x], off));
+                    R.lo[x] = fminf(R.lo[x], __shfl_xor(R.lo[x], off));
+                    R.hi[x] = fmaxf(R.hi[x], __shfl_xor(R.hi[x], off));
+                }
+            wave_fence();
+            if (lane == 0) {
+                const int mid = lo + n_left, node = task.z;
+                const int4 child[2] = {make_int4(lo, mid, node + 1, (level + 1) & 1),
+                                       make_int4(mid, hi, node + n_left, (level + 1) & 1)};
+                int ref[2];
+                for (int k = 0; k < 2; k++) {
+                    const int size = child[k].y - child[k].x;
+                    ref[k] = size == 1 ? ~sah_load(out, child[k].x).id : child[k].z;
+                    if (size > kSahSmall) list[(level + 1) & 1][atomicAdd(&count[(level + 1) & 1], 1)] = child[k];
+                    else if (size > 1) small[atomicAdd(&n_small, 1)] = child[k];
+                }
+                node_store(nodes, node, L, R, ref[0], ref[1]);
+            }
+        }
+        __threadfence_block();
+        __syncthreads();
+        if (threadIdx.x == 0) count[level & 1] = 0;
+        __syncthreads();
+    }
+    // depth of the Karras tree: dep = links followed so far, par = where they lead
+    const int n_int = n - 1;
+    for (int i = threadIdx.x; i < n_int; i += kSahBlock) dep[i] = i > 0 ? 1 : 0;
+    if (threadIdx.x == 0) par[0] = 0;
+    for (int i = threadIdx.x; i < n_int; i += kSahBlock) {
+        const int2 r = node_refs(karras, i);
+        if (r.x >= 0) par[r.x] = (unsigned short)i;
+        if (r.y >= 0) par[r.y] = (unsigned short)i;
+    }
+    __syncthreads();
+    constexpr int kEach = kSahMax / kSahBlock;
+    int deepest = 0;
+    for (int step = 1; step < n_int; step *= 2) {
+        unsigned short p2[kEach], d2[kEach];
+        for (int k = 0; k < kEach; k++) {
+            const int i = threadIdx.x + k * kSahBlock;
+            if (i < n_int) {
+                p2[k] = par[par[i]];
+                d2[k] = dep[i] + dep[par[i]];
+            }
+        }
+        __syncthreads();
+        for (int k = 0; k < kEach; k++) {
+            const int i = threadIdx.x + k * kSahBlock;
+            if (i < n_int) {
+                par[i] = p2[k];
+                dep[i] = d2[k];
+            }
+        }
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < n_int; i += kSahBlock) deepest = max(deepest, (int)dep[i] + 1);
+    for (int off = 32; off >= 1; off >>= 1) deepest = max(deepest, __shfl_xor(deepest, off));
+    if (lane == 0) atomicMax(&st->max_depth, deepest);
+    if (threadIdx.x == 0) st->n_small = n_small;
+}
+
+// One wavefront per subtree of at most kSahSmall triangles, one triangle per
+// lane, all nodes of a level at once: a node's triangles are the lanes [s, e),
+// each tries the plane at its own centre on the three axes, and the cheapest
+// sorts them in two.
+constexpr int kSmallBlock = 256;
+__global__ void __launch_bounds__(kSmallBlock) k_sah_small(float4* __restrict__ nodes,
+                                                           const float4* __restrict__ buf0, const float4* __restrict__ buf1,
+                                                           const int4* __restrict__ small,
+                                                           const BuildState* __restrict__ st) {
+    struct Lane {
+        Box box[64];
+        int id[64];
+        float cost[64];
+        int axis[64], left[64];
+    };
+    __shared__ Lane sh[kSmallBlock / 64];
+    const int lane = threadIdx.x & 63;
+    Lane& w = sh[threadIdx.x >> 6];
+    const int n_small = st->n_small;
+    for (int t = blockIdx.x * (kSmallBlock / 64) + (threadIdx.x >> 6); t < n_small; t += gridDim.x * (kSmallBlock / 64)) {
+        const int4 task = small[t];
+        const int m = task.y - task.x;
+        int s = lane < m ? 0 : lane, e = lane < m ? m : lane, node = task.z;
+        const SahBox own = sah_load(task.w ? buf1 : buf0, task.x + min(lane, m - 1));
+        int id = own.id;
+        Box b = own.box;
+        while (__ballot(e - s > 1)) {
+            w.box[lane] = b;
+            wave_fence();
+            float key[3];
+            for (int a = 0; a < 3; a++) key[a] = box_centre(b, a);
+            Box L[3] = {kNoBox, kNoBox, kNoBox}, R[3] = {kNoBox, kNoBox, kNoBox};
+            int nl[3] = {0, 0, 0};
+            for (int j = s; j < e; j++) {
+                const Box o = w.box[j];
+                for (int a = 0; a < 3; a++) {
+                    const float k = box_centre(o, a);
+                    const bool left = k < key[a] || (k == key[a] && j <= lane);
+                    box_add_if(L[a], o, left);
+                    box_add_if(R[a], o, !left);
+                    nl[a] += left ? 1 : 0;
+                }
+            }
+            float cost = INFINITY;
+            int axis = 0, mine = 0;
+            Box bl = kNoBox, br = kNoBox;
+#pragma unroll
+            for (int a = 0; a < 3; a++) {
+                const float c = nl[a] < e - s ? split_cost(L[a], nl[a], R[a], e - s - nl[a]) : INFINITY;
+                const bool take = c < cost;
+                cost = take ? c : cost;
+                axis = take ? a : axis;
+                mine = take ? nl[a] : mine;
+                for (int x = 0; x < 3; x++) {
+                    bl.lo[x] = take ? L[a].lo[x] : bl.lo[x];
+                    bl.hi[x] = take ? L[a].hi[x] : bl.hi[x];
+                    br.lo[x] = take ? R[a].lo[x] : br.lo[x];
+                    br.hi[x] = take ? R[a].hi[x] : br.hi[x];
+                }
+            }
+            w.cost[lane] = cost;
+            w.axis[lane] = axis;
+            w.left[lane] = mine;
+            wave_fence();
+            // every lane has a plane that parts its node, but for the last centre of
+            // each axis, so a node of two or more always has a finite cost
+            int win = s;
+            for (int j = s + 1; j < e; j++)
+                if (w.cost[j] < w.cost[win]) win = j;
+            const bool split = e - s > 1;
+            const int n_left = split ? w.left[win] : 0, ax = split ? w.axis[win] : 0;
+            const Box wb = w.box[split ? win : lane];
+            const float kw = ax == 0 ? box_centre(wb, 0) : ax == 1 ? box_centre(wb, 1) : box_centre(wb, 2);
+            const float k = ax == 0 ? key[0] : ax == 1 ? key[1] : key[2];
+            const bool left = split && (k < kw || (k == kw && lane <= win));
+            const unsigned long long ml = __ballot(left), mr = __ballot(split && !left);
+            const unsigned long long below = (1ull << lane) - (1ull << s);       // lanes [s, lane)
+            const int at = !split ? lane : left ? s + (int)__popcll(ml & below) : s + n_left + (int)__popcll(mr & below);
+            const bool winner = split && lane == win;
+            wave_fence();
+            w.box[at] = b;
+            w.id[at] = id;
+            wave_fence();
+            b = w.box[lane];
+            id = w.id[lane];
+            if (winner)
+                node_store(nodes, node, bl, br, n_left == 1 ? ~w.id[s] : node + 1,
+                           e - s - n_left == 1 ? ~w.id[s + n_left] : node + n_left);
+            if (split) {
+                if (lane < s + n_left) {
+                    e = s + n_left;
+                    node = node + 1;
+                } else {
+                    s = s + n_left;
+                    node = node + n_left;
+                }
+            }
+            wave_fence();
+        }
+    }
+}
+
 // One level of wide nodes, entries {node, depth} of `cur`: marks their internal
 // children and appends them to `next` (one atomic on *total per block and
 // round; `total` may lie in LDS).  Every thread of the block calls it.
@@ -633,7 +1033,8 @@ __device__ __forceinline__ void wide_level(const float4* __restrict__ nodes, con
     }
 }
 
-__device__ __forceinline__ void report_depth(int deepest, BuildState* __restrict__ st) {
+__device__ __forceinline__ void report_depth(int deepest, BuildState* __restrict__ st, bool wanted) {
+    if (!wanted) return;
     for (int off = 32; off >= 1; off >>= 1) deepest = max(deepest, __shfl_xor(deepest, off));
     if ((threadIdx.x & 63) == 0 && deepest > 0) atomicMax(&st->max_depth, deepest);
 }
@@ -644,7 +1045,7 @@ __device__ __forceinline__ void report_depth(int deepest, BuildState* __restrict
 constexpr int kTopBlock = 1024;
 __global__ void __launch_bounds__(kTopBlock) k_wide_top(const float4* __restrict__ nodes, int64_t n_int,
                                                         int2* lists, unsigned* __restrict__ flags,
-                                                        BuildState* __restrict__ st) {
+                                                        BuildState* __restrict__ st, bool depth) {
     __shared__ int n_next;
     int deepest = 0, count = 1, level = 0;
     if (threadIdx.x == 0) {
@@ -666,18 +1067,18 @@ __global__ void __launch_bounds__(kTopBlock) k_wide_top(const float4* __restrict
         __syncthreads();
     }
     if (threadIdx.x == 0) st->next_level = level;
-    report_depth(deepest, st);
+    report_depth(deepest, st, depth);
 }
 
 __global__ void __launch_bounds__(kBlock) k_wide_level(const float4* __restrict__ nodes, int64_t n_int, int level,
                                                        int2* lists, unsigned* __restrict__ flags,
-                                                       BuildState* __restrict__ st) {
+                                                       BuildState* __restrict__ st, bool depth) {
     if (level < st->next_level) return;
     const int count = st->count[level];
     int deepest = 0;
     wide_level(nodes, lists + (level & 1) * n_int, count, lists + ((level + 1) & 1) * n_int, &st->count[level + 1], flags,
                blockIdx.x * kBlock, gridDim.x * kBlock, deepest);
-    report_depth(deepest, st);
+    report_depth(deepest, st, depth);
 }
 
 // Writes the wide nodes numbered below `cap` and the number of all of them.
@@ -753,7 +1154,7 @@ static int64_t rs_hist_len(int64_t n) { return 256 * ((n + kRsTile - 1) / kRsTil
 static int64_t expected_spill(int64_t n) {
     int bits = 1;
     while (((int64_t)1 << bits) < n) bits++;
-    return std::max<int64_t>(0, 3 * (bits / 2 + 4) + 2 - RT_STACK_LDS);
+    return std::max<int64_t>(0, 3 * (bits / 2 + 6) + 2 - RT_STACK_LDS);
 }
 
 // The traversal's spill area: at the end of the scene's allocation if it was
@@ -792,6 +1193,9 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
     const size_t o_keys = part(sizeof(uint64_t) * n);
     const size_t o_state = part(sizeof(BuildState));
     const size_t o_flags = part(sizeof(unsigned) * n_int), o_index = part(sizeof(unsigned) * n_int);
+    const bool sah = n >= 2 && n <= kSahMax;
+    const size_t o_sah = part(sah ? sizeof(float4) * 4 * n_int : 0), o_buf = part(sah ? 2 * sizeof(float4) * 2 * n : 0),
+                 o_small = part(sah ? sizeof(int4) * (n / 2) : 0);
     const size_t o_wide = total;
     const size_t o_k1 = part(sizeof(uint64_t) * n), o_v0 = part(sizeof(uint32_t) * n), o_v1 = part(sizeof(uint32_t) * n);
     const size_t o_hist = part(sizeof(unsigned) * (size_t)rs_hist_len(n));
@@ -831,6 +1235,7 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
     unsigned* const hist = (unsigned*)(base + o_hist);
     float4* const boxes = (float4*)(base + o_boxes);
     int2* const lists = (int2*)(base + o_k1);
+    const float4* const tree = sah ? (float4*)(base + o_sah) : s->nodes;      // what the wide nodes are made of
 
     hipEvent_t e0 = nullptr, e1 = nullptr;
     auto cleanup = [&]() {
@@ -845,7 +1250,8 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
     hipLaunchKernelGGL(k_bounds, dim3(std::min(g, 512u)), dim3(kBlock), 0, st, V, n_v, F, M, s->n_mat, n, state);
     hipLaunchKernelGGL(k_morton, dim3(std::min(g, 512u)), dim3(kBlock), 0, st, V, n_v, F, n, state, ka, va);
     const int rs_blocks = (int)((n + kRsTile - 1) / kRsTile);
-    for (int shift = 0; shift < 64; shift += 8) {
+    if (n <= kSortOne) hipLaunchKernelGGL(k_sort_one, dim3(1), dim3(kSortBlock), 0, st, ka, va, (int)n);
+    for (int shift = 0; shift < 64 && n > kSortOne; shift += 8) {
         const unsigned* const totals = state->totals[shift / 8];      // an address on the device
         hipLaunchKernelGGL(k_rs_hist, dim3(rs_blocks), dim3(kBlock), 0, st, ka, n, shift, hist, rs_blocks);
         hipLaunchKernelGGL(k_rs_offsets, dim3(256), dim3(kBlock), 0, st, hist, rs_blocks, totals);
@@ -854,19 +1260,20 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
         std::swap(ka, kb);
         std::swap(va, vb);
     }
-    // after 8 passes the sorted data is back in (morton, v0)
+    // after 8 passes (or none) the sorted data is back in (morton, v0)
     hipLaunchKernelGGL(k_gather, dim3(g), dim3(kBlock), 0, st, V, n_v, F, va, M, n, s->tris, s->normals, boxes);
     constexpr int kLevelBatch = 16, kTopLevels = 5;      // k_wide_top takes levels 0..4 at least (4^5 nodes)
-    int level = kTopLevels;
+    // no level of so few triangles has more nodes than k_wide_top takes
+    int level = n <= 2 * kTopBlock ? kMaxLevels : kTopLevels;
     int64_t wide_cap = (int64_t)(wide_bytes / wide_node);
     auto queue_levels = [&]() {
         const unsigned gl = std::min(g, 512u);
         for (int k = 0; k < kLevelBatch && level < kMaxLevels; k++, level++)
-            hipLaunchKernelGGL(k_wide_level, dim3(gl), dim3(kBlock), 0, st, s->nodes, n_int, level, lists, flags, state);
+            hipLaunchKernelGGL(k_wide_level, dim3(gl), dim3(kBlock), 0, st, tree, n_int, level, lists, flags, state, !sah);
     };
     auto queue_emit = [&](float4* wide, int64_t cap) {
         scan_exclusive(flags, index4, n_int, hist, st);
-        hipLaunchKernelGGL(k_wide_emit, dim3(g), dim3(kBlock), 0, st, s->nodes, s->tris, flags, index4, n_int, cap, wide,
+        hipLaunchKernelGGL(k_wide_emit, dim3(g), dim3(kBlock), 0, st, tree, s->tris, flags, index4, n_int, cap, wide,
                            state);
     };
     if (n_int > 0) {
@@ -879,7 +1286,15 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
             }
         }
         hipLaunchKernelGGL(k_hierarchy, dim3(g), dim3(kBlock), 0, st, ka, n, boxes, levels, s->nodes);
-        hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, s->nodes, n_int, lists, flags, state);
+        if (sah) {
+            float4* const buf = (float4*)(base + o_buf);
+            int4* const small = (int4*)(base + o_small);
+            hipLaunchKernelGGL(k_sah_top, dim3(1), dim3(kSahBlock), 0, st, boxes, (int)n, s->nodes, (float4*)tree, buf,
+                               buf + 2 * n, small, state);
+            hipLaunchKernelGGL(k_sah_small, dim3((unsigned)std::min<int64_t>(256, (n + 31) / 32)), dim3(kSmallBlock), 0, st,
+                               (float4*)tree, buf, buf + 2 * n, small, state);
+        }
+        hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, tree, n_int, lists, flags, state, !sah);
         queue_levels();
         queue_emit((float4*)(base + o_wide), wide_cap);
     }
@@ -907,7 +1322,7 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
             }
             const int upto = level + kLevelBatch;
             hipLaunchKernelGGL(k_build_init, dim3(std::min(g, 1024u)), dim3(kBlock), 0, st, state, flags, n_int);
-            hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, s->nodes, n_int, lists, flags, state);
+            hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, tree, n_int, lists, flags, state, !sah);
             level = kTopLevels;
             while (level < std::min(upto, kMaxLevels)) queue_levels();
             queue_emit((float4*)(base + o_wide), wide_cap);
@@ -919,6 +1334,7 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
                 h.lo[a] = first.lo[a];
                 h.hi[a] = first.hi[a];
             }
+            if (sah) h.max_depth = first.max_depth;
         }
         s->root = 0;
         s->depth = h.max_depth;
