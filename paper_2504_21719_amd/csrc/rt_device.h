@@ -34,14 +34,45 @@ __device__ __forceinline__ cf cdiv(cf a, cf b) {
     float inv = __builtin_amdgcn_rcpf(cabs2(b));
     return cf{(a.re * b.re + a.im * b.im) * inv, (a.im * b.re - a.re * b.im) * inv};
 }
-// Principal square root (Re >= 0).  With m = |z| and t = sqrt((m + |x|)/2):
-//   x >= 0:  sqrt(z) = t + j y/(2t)
-//   x < 0:   sqrt(z) = |y|/(2t) + j sign(y) t
-// so that m +- x never cancels.  Both are selected, not branched to.  Hardware
-// square root and reciprocal (about 1 ulp each).
+// Product, quotient and sum of two scaled numbers with every rounding written
+// out: the compiler's own choice of what to contract depends on the code
+// around, and a transfer matrix would differ in its last bits from kernel to
+// kernel (the orientation gradient, a sum that cancels by factors of 1e4,
+// shows them).
+__device__ __forceinline__ cf cmul_exact(cf a, cf b) {
+#pragma clang fp contract(off)
+    return cf{__builtin_fmaf(b.re, a.re, -(b.im * a.im)), __builtin_fmaf(b.im, a.re, b.re * a.im)};
+}
+__device__ __forceinline__ cf cdiv_exact(cf a, cf b) {
+#pragma clang fp contract(off)
+    const float inv = __builtin_amdgcn_rcpf(__builtin_fmaf(b.re, b.re, b.im * b.im));
+    return cf{__builtin_fmaf(a.re, b.re, a.im * b.im) * inv, __builtin_fmaf(a.im, b.re, -(a.re * b.im)) * inv};
+}
+__device__ __forceinline__ cf cmix_exact(cf a, float wa, cf b, float wb) {
+#pragma clang fp contract(off)
+    return cf{__builtin_fmaf(a.re, wa, b.re * wb), __builtin_fmaf(a.im, wa, b.im * wb)};
+}
+// Principal square root (Re >= 0).  With m = |z|:
+//   Re >= 0 branch:  t = sqrt((m + x)/2),  sqrt(z) = t + j y/(2t)
+//   x < 0:           t = sqrt((m - x)/2),  sqrt(z) = |y|/(2t) + j sign(y) t
+// choosing the branch that avoids cancellation in m +- x.  Hardware square
+// root and reciprocal (about 1 ulp each).
 __device__ __forceinline__ cf csqrt_principal(cf z) {
+    float x = z.re, y = z.im;
+    float m = __builtin_amdgcn_sqrtf(x * x + y * y);
+    if (m == 0.0f) return cf{0.0f, 0.0f};
+    if (x >= 0.0f) {
+        float t = __builtin_amdgcn_sqrtf(0.5f * (m + x));
+        return cf{t, y * __builtin_amdgcn_rcpf(2.0f * t)};
+    }
+    float t = __builtin_amdgcn_sqrtf(0.5f * (m - x));
+    return cf{fabsf(y) * __builtin_amdgcn_rcpf(2.0f * t), copysignf(t, y)};
+}
+// The same bits, selected instead of branched to, for the ray loop.
+__device__ __forceinline__ cf csqrt_selected(cf z) {
+#pragma clang fp contract(off)
     const float x = z.re, y = z.im;
-    const float m = __builtin_amdgcn_sqrtf(x * x + y * y);
+    const float m = __builtin_amdgcn_sqrtf(__builtin_fmaf(x, x, y * y));
     const float t = __builtin_amdgcn_sqrtf(0.5f * (m + fabsf(x)));
     const float h = y * __builtin_amdgcn_rcpf(2.0f * t);
     const bool right = x >= 0.0f;

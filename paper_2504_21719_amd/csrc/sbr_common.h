@@ -590,6 +590,18 @@ struct Fresnel {
 template <bool DERIV>
 __device__ __forceinline__ Fresnel fresnel(float c, cf eta) {
     Fresnel F;
+    if (!DERIV) {
+#pragma clang fp contract(off)
+        const cf s = csqrt_selected(cf{eta.re - __builtin_fmaf(-c, c, 1.0f), eta.im});
+        const cf lp = cf{__builtin_fmaf(eta.re, c, s.re), __builtin_fmaf(eta.im, c, s.im)};
+        const cf lm = cf{__builtin_fmaf(eta.re, c, -s.re), __builtin_fmaf(eta.im, c, -s.im)};
+        F.rperp = cdiv_exact(cf{c - s.re, -s.im}, cf{c + s.re, s.im});
+        F.rpar = cdiv_exact(lm, lp);
+        F.s = s;
+        F.drperp = cf{0, 0};
+        F.drpar = cf{0, 0};
+        return F;
+    }
     cf s = csqrt_principal(cf{eta.re - (1.0f - c * c), eta.im});
     cf cp = cf{c + s.re, s.im};
     cf cm = cf{c - s.re, -s.im};
@@ -598,17 +610,12 @@ __device__ __forceinline__ Fresnel fresnel(float c, cf eta) {
     F.rperp = cdiv(cm, cp);
     F.rpar = cdiv(lm, lp);
     F.s = s;
-    if (DERIV) {
-        // r_perp = (c - s)/(c + s), s = sqrt(eta - sin^2): d r_perp/d eta = -c / (s (c + s)^2)
-        // r_par = (eta c - s)/(eta c + s): d r_par/d eta = c (eta - 2 sin^2) / (s (eta c + s)^2)
-        cf scp2 = cmul(s, cmul(cp, cp));
-        F.drperp = cdiv(cf{-c, 0.0f}, scp2);
-        cf num = cscale(cf{eta.re - 2.0f * (1.0f - c * c), eta.im}, c);
-        F.drpar = cdiv(num, cmul(s, cmul(lp, lp)));
-    } else {
-        F.drperp = cf{0, 0};
-        F.drpar = cf{0, 0};
-    }
+    // r_perp = (c - s)/(c + s), s = sqrt(eta - sin^2): d r_perp/d eta = -c / (s (c + s)^2)
+    // r_par = (eta c - s)/(eta c + s): d r_par/d eta = c (eta - 2 sin^2) / (s (eta c + s)^2)
+    cf scp2 = cmul(s, cmul(cp, cp));
+    F.drperp = cdiv(cf{-c, 0.0f}, scp2);
+    cf num = cscale(cf{eta.re - 2.0f * (1.0f - c * c), eta.im}, c);
+    F.drpar = cdiv(num, cmul(s, cmul(lp, lp)));
     return F;
 }
 

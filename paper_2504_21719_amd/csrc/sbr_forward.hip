@@ -609,15 +609,13 @@ struct FieldState<0> {
     // whose second vector is -e_par of the outgoing wave for both k' = k_r and
     // k' = k
     __device__ __forceinline__ void interact(const Bounce& b, cf cperp, cf cpar) {
-        cf na = cadd(cscale(Ta, b.w00), cscale(Tc, b.w01));
-        cf nb = cadd(cscale(Tb, b.w00), cscale(Td, b.w01));
-        cf nc = cadd(cscale(Ta, b.w10), cscale(Tc, b.w11));
-        cf nd = cadd(cscale(Tb, b.w10), cscale(Td, b.w11));
-        Ta = cmul(cperp, na);
-        Tb = cmul(cperp, nb);
-        cf mr = cf{-cpar.re, -cpar.im};
-        Tc = cmul(mr, nc);
-        Td = cmul(mr, nd);
+        const cf na = cmix_exact(Ta, b.w00, Tc, b.w01), nb = cmix_exact(Tb, b.w00, Td, b.w01);
+        const cf nc = cmix_exact(Ta, b.w10, Tc, b.w11), nd = cmix_exact(Tb, b.w10, Td, b.w11);
+        const cf mr = cf{-cpar.re, -cpar.im};
+        Ta = cmul_exact(cperp, na);
+        Tb = cmul_exact(cperp, nb);
+        Tc = cmul_exact(mr, nc);
+        Td = cmul_exact(mr, nd);
     }
 };
 
