@@ -187,39 +187,61 @@ __device__ __forceinline__ Launch fib_launch(int64_t n, int64_t N) {
     return L;
 }
 
-// sin and cos of the angle (pi/2) v for v in quarter turns: v is split at
-// the nearest integer q (exact in FP64), the remainder y = (pi/2)(v - q),
-// |y| <= pi/4, is taken to FP32, sin y and cos y come from their Taylor
-// series to y^9 and y^10 (truncation below 2e-9 on |y| <= pi/4), and the
-// quadrant q mod 4 rotates the pair.
+// sin and cos of the angle (pi/2) v for v in quarter turns (|v| < 2^51): v is
+// split at the nearest integer q (exact in FP64; adding 1.5 2^52 rounds to it and
+// leaves it in the low bits), the remainder y = (pi/2)(v - q), |y| <= pi/4, is
+// taken to FP32, sin y and cos y come from their Taylor series to y^9 and y^10
+// (truncation below 2e-9 on |y| <= pi/4), and the quadrant q mod 4 swaps the
+// pair and sets its signs.
 __device__ __forceinline__ void sincos_quarter_turns(double v, float& s, float& c) {
-    const double q = rint(v);
+    const double big = v + 0x1.8p52;
+    const double q = big - 0x1.8p52;
+    const unsigned quad = (unsigned)__double_as_longlong(big);
     const float y = (float)((v - q) * (0.5 * RT_PI));
     const float y2 = y * y;
-    const float sy =
-        y * (1.0f + y2 * (-1.0f / 6.0f + y2 * (1.0f / 120.0f + y2 * (-1.0f / 5040.0f + y2 * (1.0f / 362880.0f)))));
-    const float cy = 1.0f + y2 * (-0.5f + y2 * (1.0f / 24.0f + y2 * (-1.0f / 720.0f +
-                                                                     y2 * (1.0f / 40320.0f - y2 / 3628800.0f))));
-    const int quad = (int)((long long)q & 3);
-    s = quad == 0 ? sy : quad == 1 ? cy : quad == 2 ? -sy : -cy;
-    c = quad == 0 ? cy : quad == 1 ? -sy : quad == 2 ? -cy : sy;
+    float ps = __builtin_fmaf(y2, 1.0f / 362880.0f, -1.0f / 5040.0f);
+    ps = __builtin_fmaf(ps, y2, 1.0f / 120.0f);
+    ps = __builtin_fmaf(ps, y2, -1.0f / 6.0f);
+    const float sy = __builtin_fmaf(y * y2, ps, y);
+    float pc = __builtin_fmaf(y2, -1.0f / 3628800.0f, 1.0f / 40320.0f);
+    pc = __builtin_fmaf(pc, y2, -1.0f / 720.0f);
+    pc = __builtin_fmaf(pc, y2, 1.0f / 24.0f);
+    pc = __builtin_fmaf(pc, y2, -0.5f);
+    const float cy = __builtin_fmaf(pc, y2, 1.0f);
+    const bool odd = quad & 1u;
+    // sin changes its sign in quadrants 2 and 3, cos in 1 and 2
+    s = __uint_as_float(__float_as_uint(odd ? cy : sy) ^ ((quad << 30) & 0x80000000u));
+    c = __uint_as_float(__float_as_uint(odd ? sy : cy) ^ (((quad + 1u) << 30) & 0x80000000u));
 }
 
 // |alpha|^2 of a synthetic transmit array for launch direction k
 // (Sec. "Handling Multiple Transmit Antennas"): alpha = a_tx^T u_P with the
 // array response a_tx[i] = exp(j 2 pi/lambda k.d_i) of
 // eq. path-solver-array-response-vector.  The phase is formed in FP64 in
-// quarter turns; the element data are the same for every lane.
+// quarter turns; the element data are the same for every lane.  VALU-bound, 32
+// instructions per element (49 before: the direction is scaled once per ray, the
+// quadrant comes from the rounded sum's bits instead of a 64-bit conversion and
+// three compares, there is no division), with the elements read through the
+// scalar cache (before, by a vector load of one address on every lane and a wait
+// for it per element): 64 elements and 1e7 rays in the city 1.40 -> 0.84 ms, of
+// which 0.54 without the array.
 __device__ __forceinline__ float array_gain(const Launch& L, const TxDesc& t) {
+    const double kx = L.kx * t.four_inv_lambda, ky = L.ky * t.four_inv_lambda, kz = L.kz * t.four_inv_lambda;
+    // read through the scalar cache: nothing writes them while the kernel runs
+    typedef const __attribute__((address_space(4))) double* sdouble;
+    typedef const __attribute__((address_space(4))) float* sfloat;
+    const sdouble pos = (sdouble)(uintptr_t)t.ant_pos;
+    const sfloat pre = (sfloat)(uintptr_t)t.precoding;
     float are = 0.0f, aim = 0.0f;
+#pragma unroll 2
     for (int i = 0; i < t.n_ant; i++) {
-        const double* d = t.ant_pos + 3 * (int64_t)i;
-        const double v = (L.kx * d[0] + L.ky * d[1] + L.kz * d[2]) * t.four_inv_lambda;
+        const double v = fma(kx, pos[3 * i], fma(ky, pos[3 * i + 1], kz * pos[3 * i + 2]));
         float s, c;
         sincos_quarter_turns(v, s, c);
-        const float ur = t.precoding[2 * (int64_t)i], ui = t.precoding[2 * (int64_t)i + 1];
-        are += ur * c - ui * s;
-        aim += ur * s + ui * c;
+        const float ur = pre[2 * i], ui = pre[2 * i + 1];
+        // one rounding at the sum's size per element
+        are += __builtin_fmaf(ur, c, -(ui * s));
+        aim += __builtin_fmaf(ur, s, ui * c);
     }
     return are * are + aim * aim;
 }
