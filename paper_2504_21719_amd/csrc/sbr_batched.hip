@@ -31,7 +31,13 @@
 //    took 1.13 ms; geometry in LDS shared by the block's wavefronts (157
 //    VGPRs) with wavefront deposits took 0.74 ms; with the forward fields
 //    in LDS as well for paths of at most six segments (124 VGPRs, four
-//    wavefronts per SIMD) it takes 0.66 ms.
+//    wavefronts per SIMD) 0.66 ms; with sums by data-parallel primitives in
+//    place of LDS permutes (84 per wavefront and sample for the gradients),
+//    material sums for the materials there are rather than eight, a selected
+//    square root and the bounce geometry on the three wavefronts that do not
+//    compute launches 0.53 ms.  Without gradients it is bound by the map's
+//    atomics (37 per ns over 16 maps of 1e6 cells; dealing neighbouring rays to one
+//    XCD changes nothing).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -70,11 +76,6 @@ struct SampArgs {
     float k0;               // 2 pi / lambda
 };
 
-__device__ __forceinline__ float wave_sum_f(float v) {
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
 // Deposit of one crossing per lane (cell < 0: none) into the map of the
 // lane's transmitter slot: at most four groups of lanes with the same slot
 // and cell are summed across the wavefront before one atomic each; lanes
@@ -88,12 +89,12 @@ __device__ __forceinline__ void deposit_wave(float* map, int cell, float w, int 
             if (!done) unsafeAtomicAdd(map + cell, w);
             break;
         }
-        const int leader = __ffsll((long long)pend) - 1;
-        const int lc = __shfl(cell, leader), ls = __shfl(slot, leader);
+        const int leader = __builtin_ctzll(pend);
+        const int lc = __builtin_amdgcn_readlane(cell, leader), ls = __builtin_amdgcn_readlane(slot, leader);
         const bool mine = !done && cell == lc && slot == ls;
         const unsigned long long grp = __ballot(mine);
-        const float v = wave_sum_f(mine ? w : 0.0f);
-        if (lane == leader) unsafeAtomicAdd(map + lc, v);
+        const float v = wave_sum(mine ? w : 0.0f);
+        if (lane == leader) unsafeAtomicAdd(map + cell, v);
         if (mine) done = true;
         pend &= ~grp;
     }
@@ -184,8 +185,9 @@ __global__ void __launch_bounds__(kSampBlock) k_samples(const SampArgs a) {
             sh.hdr[8][lane] = kap;
         }
         // ---- bounce geometry of every (segment, ray), all lanes of the block
-        for (int it = threadIdx.x; it < NSEG * kSampRays; it += blockDim.x) {
-            const int l = it / kSampRays, r = it % kSampRays;
+        // but wavefront 0 of several, which has as much to do with the launches
+        for (int l = n_wv > 1 ? wv - 1 : 0; l >= 0 && l < NSEG; l += max(1, n_wv - 1)) {
+            const int r = lane;
             const int64_t g = g0 + r;
             if (g >= T) continue;
             const int ns = a.nseg[g];
@@ -287,7 +289,7 @@ __global__ void __launch_bounds__(kSampBlock) k_samples(const SampArgs a) {
                     if (l == 0) continue;
                     const int k = l - 1;      // the bounce that ends segment l-1
                     const int m = sh.mc[k][0][lane];
-                    Fresnel F = fresnel<true>(sh.geo[k][4][lane], cf{eps[m], -sig[m] * a.pl.inv_eps0_omega});
+                    Fresnel F = fresnel<true, true>(sh.geo[k][4][lane], cf{eps[m], -sig[m] * a.pl.inv_eps0_omega});
                     if (SLAB) {
                         cf tp, tl, dtp, dtl;
                         slab_grad(F, a.k0 * a.thickness[m], tp, tl, dtp, dtl);
@@ -301,6 +303,7 @@ __global__ void __launch_bounds__(kSampBlock) k_samples(const SampArgs a) {
                     cf z = csub(cmulc(lam0, cmul(F.drperp, u0)), cmulc(lam1, cmul(F.drpar, u1)));
 #pragma unroll
                     for (int jj = 0; jj < kMaxMat; jj++) {
+                        if (jj >= a.n_mat) break;
                         if (jj == m) {
                             ge[jj] += 2.0f * z.re;
                             gs[jj] += 2.0f * z.im * a.pl.inv_eps0_omega;
@@ -326,23 +329,24 @@ __global__ void __launch_bounds__(kSampBlock) k_samples(const SampArgs a) {
                 unsigned long long pend = __ballot(valid);
                 bool done = !valid;
                 while (pend) {
-                    int leader = __ffsll((long long)pend) - 1;
-                    int lt = __shfl(tx_i, leader);
-                    bool mine = !done && tx_i == lt;
-                    unsigned long long grp = __ballot(mine);
+                    const int lt = __builtin_amdgcn_readlane(tx_i, __builtin_ctzll(pend));
+                    const bool mine = !done && tx_i == lt;
+                    const unsigned long long grp = __ballot(mine);
                     const int64_t w0 = a.woff[lt], nw = a.woff[lt + 1] - w0;
                     double* dst = a.gws + w0 * S * a.P + (int64_t)s * a.P * nw + (gw - (a.prefix[lt] >> 6));
-                    for (int j = 0; j < a.n_mat && j < kMaxMat; j++) {
-                        double v = wsum(mine ? (double)ge[j] : 0.0);
-                        double u = wsum(mine ? (double)gs[j] : 0.0);
-                        if (lane == leader) {
+#pragma unroll
+                    for (int j = 0; j < kMaxMat; j++) {
+                        if (j >= a.n_mat) break;
+                        const double v = wave_sum_63(mine ? (double)ge[j] : 0.0);
+                        const double u = wave_sum_63(mine ? (double)gs[j] : 0.0);
+                        if (lane == 63) {
                             dst[j * nw] = v;
                             dst[(a.n_mat + j) * nw] = u;
                         }
                     }
                     for (int j = 0; j < 3; j++) {
-                        double v = wsum(mine ? (double)go[j] : 0.0);
-                        if (lane == leader) dst[(2 * a.n_mat + j) * nw] = v;
+                        const double v = wave_sum_63(mine ? (double)go[j] : 0.0);
+                        if (lane == 63) dst[(2 * a.n_mat + j) * nw] = v;
                     }
                     if (mine) done = true;
                     pend &= ~grp;

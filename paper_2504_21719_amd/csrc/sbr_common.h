@@ -75,6 +75,41 @@ __device__ __forceinline__ int64_t launch_index(const LaunchOrder& o, int64_t n)
     return n - r + fib_mod((double)r * (double)kFib.e[i].inv, kFib.e[i]);
 }
 
+// ------------------------------------------------------------ wavefront sums
+// Sum over the wavefront (every lane active), the same on every lane: rows of
+// 16 by shifts, then across the rows, all on the VALU's data-parallel
+// primitives (a butterfly through the LDS permute took six LDS round trips).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v = dpp_add<0x111, 0xf>(v);      // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);      // lane 15 of rows 0 and 2 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);      // lane 31 into rows 2 and 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// The same in FP64, for lane 63 only.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum_63(double v) {
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);
+    return dpp_add<0x143, 0xc>(v);
+}
+
 // ---------------------------------------------------------------- duals
 // FP32 forward-mode scalar carrying d/d(yaw, pitch, roll).
 struct d3f {
@@ -608,8 +643,9 @@ struct Fresnel {
     cf s;                 // sqrt(eta - sin^2 theta_1), principal branch
 };
 
-// c = cos(theta_1) >= 0, eta = eps_r - j sigma/(eps0 omega)  (eq. eta)
-template <bool DERIV>
+// c = cos(theta_1) >= 0, eta = eps_r - j sigma/(eps0 omega)  (eq. eta).  With
+// SELECT the derivatives' square root is selected too.
+template <bool DERIV, bool SELECT = false>
 __device__ __forceinline__ Fresnel fresnel(float c, cf eta) {
     Fresnel F;
     if (!DERIV) {
@@ -624,7 +660,8 @@ __device__ __forceinline__ Fresnel fresnel(float c, cf eta) {
         F.drpar = cf{0, 0};
         return F;
     }
-    cf s = csqrt_principal(cf{eta.re - (1.0f - c * c), eta.im});
+    const cf z = cf{eta.re - (1.0f - c * c), eta.im};
+    cf s = SELECT ? csqrt_selected(z) : csqrt_principal(z);
     cf cp = cf{c + s.re, s.im};
     cf cm = cf{c - s.re, -s.im};
     cf ec = cscale(eta, c);

@@ -172,23 +172,6 @@ __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q,
 // each other on the city and the 1.02 M-triangle scene).
 constexpr int kPacketWaste = 8;
 
-// Sum over the wavefront (every lane active), the same on every lane: rows of
-// 16 by shifts, then across the rows, all on the VALU's data-parallel
-// primitives (a butterfly through the LDS permute took six LDS round trips).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_add(float v) {
-    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
-}
-__device__ __forceinline__ float wave_sum(float v) {
-    v = dpp_add<0x111, 0xf>(v);      // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);      // lane 15 of rows 0 and 2 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);      // lane 31 into rows 2 and 3
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
 // The kernel's argument block, with its address hidden from the optimiser:
 // each part of the ray loop reads the arguments it needs through the scalar
 // cache.  Without this the compiler loads all of them before the loop, runs
