@@ -17,6 +17,10 @@
 
 namespace rtd {
 
+// Lanes on which v holds (the library's takes an int, which costs a select and a
+// compare where v is not a single comparison).
+__device__ __forceinline__ unsigned long long ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+
 // round(2^64 (phi_g - 1)): frac(n / phi_g) = frac(n (phi_g - 1)) = (n * C mod 2^64) / 2^64
 constexpr uint64_t kPhiFrac = 0x9e3779b97f4a7c16ull;
 
@@ -461,8 +465,9 @@ __device__ __forceinline__ unsigned med3_u32(unsigned a, unsigned b, unsigned c)
 // FP64, which is what makes shared edges watertight.
 // The part after the shear: returns whether the ray hits at t > t_min.
 // Straight-line but for the FP64 retry, which a wavefront enters only if one
-// of its lanes needs it: in a wavefront whose lanes test the same triangle an
-// early exit is seldom taken by all of them, and each costs a branch.
+// of its lanes needs it, and one exit where no lane is inside: in a wavefront
+// whose lanes test the same triangle other exits are seldom taken by all of
+// them, and each costs a branch.
 __device__ __forceinline__ bool tri_sheared(float sz, float Ax, float Ay, float Ak, float Bx, float By, float Bk,
                                             float Cx, float Cy, float Ck, float t_min, float& t) {
 #pragma clang fp contract(off)
@@ -470,7 +475,7 @@ __device__ __forceinline__ bool tri_sheared(float sz, float Ax, float Ay, float 
     float V = Ax * Cy - Ay * Cx;
     float W = Bx * Ay - By * Ax;
     const bool zero = (U == 0.0f) | (V == 0.0f) | (W == 0.0f);
-    if (__builtin_expect(__ballot(zero) != 0ull, 0)) {
+    if (__builtin_expect(ballot(zero) != 0ull, 0)) {
         if (zero) {
             U = (float)((double)Cx * (double)By - (double)Cy * (double)Bx);
             V = (float)((double)Ax * (double)Cy - (double)Ay * (double)Cx);
@@ -478,6 +483,8 @@ __device__ __forceinline__ bool tri_sheared(float sz, float Ax, float Ay, float 
         }
     }
     const bool out = (min3_raw(U, V, W) < 0.0f) & (max3_raw(U, V, W) > 0.0f);
+    t = 0.0f;
+    if (ballot(!out) == 0ull) return false;
     const float det = U + V + W;
     const float Az = sz * Ak, Bz = sz * Bk, Cz = sz * Ck;
     const float T = U * Az + V * Bz + W * Cz;
@@ -808,7 +815,7 @@ __device__ __forceinline__ float3 te_direction(float3 k, float3 n) {
     float3 e = cross3(k, n);
     float l2 = dot3(e, e);
     const bool normal = l2 < 1e-14f;
-    if (__builtin_expect(__ballot(normal) != 0ull, 0)) {
+    if (__builtin_expect(ballot(normal) != 0ull, 0)) {
         if (normal) {
             float ax = fabsf(k.x), ay = fabsf(k.y), az = fabsf(k.z);
             float3 a = (ax <= ay && ax <= az) ? f3(1, 0, 0) : (ay <= az ? f3(0, 1, 0) : f3(0, 0, 1));

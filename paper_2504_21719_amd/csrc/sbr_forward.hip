@@ -257,6 +257,13 @@ __device__ __forceinline__ void take_hit(Best& b, bool hit, float t, int id, int
     b.lim = better ? fminf(t * kBoxSlack, FLT_MAX) : b.lim;
 }
 
+// Set bits of a mask, counted and kept in scalar registers.
+__device__ __forceinline__ int count_lanes(unsigned long long m) {
+    int n;
+    asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(m) : "scc");
+    return n;
+}
+
 // Value i (0..3, from its two lowest bits) of four.
 template <typename T>
 __device__ __forceinline__ T pick4(T v0, T v1, T v2, T v3, unsigned i) {
@@ -293,10 +300,10 @@ __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int
     // permutation of the triangle test
     const int nx = uniform((int)r.nx), ny = uniform((int)r.ny), nz = uniform((int)r.nz);
     const int kx = uniform(r.kx), ky = uniform(r.ky), kz = uniform(r.kz);
-    const unsigned long long act = __ballot(true);
-    const int n_act = (int)__popcll(act);
+    const unsigned long long act = ballot(true);
+    const int n_act = count_lanes(act);
     node_out = 0;
-    if (__ballot((int)r.nx == nx && (int)r.ny == ny && (int)r.nz == nz && r.kx == kx && r.kz == kz) != act) return true;
+    if (ballot((int)r.nx == nx && (int)r.ny == ny && (int)r.nz == nz && r.kx == kx && r.kz == kz) != act) return true;
     const float ox = pick(r.ox, r.oy, r.oz, kx), oy = pick(r.ox, r.oy, r.oz, ky), oz = pick(r.ox, r.oy, r.oz, kz);
     const float4* const wide = a.wide;
     const float4* const tris = a.tris;
@@ -314,7 +321,7 @@ __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int
                              max_raw(__builtin_fmaf(w.pz[c], r.iz, r.cnz), tmin));
             const float f = min3_raw(__builtin_fmaf(w.qx[c], r.jx, r.cfx), __builtin_fmaf(w.qy[c], r.jy, r.cfy),
                                      min_raw(__builtin_fmaf(w.qz[c], r.jz, r.cfz), best.lim));
-            m[c] = __ballot(te[c] <= f);
+            m[c] = ballot(te[c] <= f);
         }
         // bit c + 1: some lane enters child c
         const unsigned hits = (m[0] ? 2u : 0u) | (m[1] ? 4u : 0u) | (m[2] ? 8u : 0u) | (m[3] ? 16u : 0u);
@@ -350,7 +357,7 @@ __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int
                 inner &= inner - 1u;
                 const int r2 = ref(c);
                 const float k2 = entry(c);
-                const bool swap = (int)__popcll(__ballot(k2 < key)) > (int)__popcll(__ballot(key < k2));
+                const bool swap = count_lanes(ballot(k2 < key)) > count_lanes(ballot(key < k2));
                 const int far_ref = swap ? next : r2;
                 if (__builtin_expect(sp < RT_STACK_LDS, 1))
                     stk[sp * lstride] = make_int2(far_ref, __float_as_int(swap ? key : k2));
@@ -362,7 +369,7 @@ __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int
             }
         }
         mine = key <= best.lim;
-        unsigned long long live = __ballot(mine);
+        unsigned long long live = ballot(mine);
         while (live == 0ull) {
             if (sp == 0) return false;
             sp--;
@@ -374,7 +381,7 @@ __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int
                 next = uniform(spill_slot(kernel_args(), sp, gtid));
                 mine = true;
             }
-            live = __ballot(mine);
+            live = ballot(mine);
         }
         node = next;
         if (__builtin_expect((unsigned)node >= (unsigned)n_wide, 0)) {
@@ -383,7 +390,7 @@ __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int
         }
         // a visit that fewer than a third of the lanes want costs more than
         // its share of the per-lane loop: leave after a few of them
-        waste = max(0, waste + n_act - 3 * (int)__popcll(live));
+        waste = max(0, waste + n_act - 3 * count_lanes(live));
         if (__builtin_expect(waste > kPacketWaste * n_act, 0)) {
             node_out = mine ? node : -1;
             return true;
@@ -479,8 +486,8 @@ __device__ __forceinline__ Best closest_hit(const FwdArgs& a, float3 o, float3 k
             if (__uint_as_float(srt[0]) <= best.lim) {
                 // seldom more than one child in any lane: one test then skips all
                 // the pushes
-                if (__ballot(__uint_as_float(srt[1]) <= best.lim)) {
-                    if (__ballot(__uint_as_float(srt[2]) <= best.lim)) {
+                if (ballot(__uint_as_float(srt[1]) <= best.lim)) {
+                    if (ballot(__uint_as_float(srt[2]) <= best.lim)) {
                         if (__uint_as_float(srt[3]) <= best.lim)
                             push_entry(a, st, child(srt[3]), __uint_as_float(srt[3]), overflow);
                         if (__uint_as_float(srt[2]) <= best.lim)
@@ -662,7 +669,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
         if (!exhausted || res_b < res_e) {
             const FwdArgs& a = kernel_args();
             const unsigned long long own = ~0ull >> (64 - a.width);
-            const unsigned long long need = __ballot(!active) & own;
+            const unsigned long long need = ballot(!active) & own;
             if (need && (__popcll(need) >= a.refill || need == own)) {
                 const unsigned cnt = (unsigned)__popcll(need);
                 // wave-uniform: every value below is the same on all lanes
@@ -762,7 +769,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                 }
             }
         }
-        if (__ballot(active) == 0ull) break;
+        if (ballot(active) == 0ull) break;
 
         // ---- closest hit of the current segment
         int slot = -1, cell = -1;
@@ -819,7 +826,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                 // wavefront; lanes left over add their own crossings (crossings
                 // scattered over many cells would otherwise cost one wavefront
                 // reduction per cell)
-                unsigned long long pend = __ballot(cell >= 0);
+                unsigned long long pend = ballot(cell >= 0);
                 bool done = cell < 0;
                 int groups = 0;
                 while (pend) {
@@ -836,13 +843,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                     bool mine = !done && cell == lc;
                     // lanes of other transmitters deposit into other maps
                     if (MODE == MODE_MULTI) mine = mine && tslot == __builtin_amdgcn_readlane(tslot, leader);
-                    unsigned long long grp = __ballot(mine);
+                    unsigned long long grp = ballot(mine);
                     float v0 = wave_sum(mine ? w0 : 0.0f);
                     float v1 = 0.0f;
                     if (two) v1 = wave_sum(mine ? w1 : 0.0f);
+                    // (the address per lane: for a uniform one the compiler would
+                    // reduce over the wavefront again)
                     if (lane == leader) {
-                        unsafeAtomicAdd(map + lc, v0);
-                        if (two) unsafeAtomicAdd(map + a.map_stride + lc, v1);
+                        unsafeAtomicAdd(map + cell, v0);
+                        if (two) unsafeAtomicAdd(map + a.map_stride + cell, v1);
                     }
                     if (mine) done = true;
                     pend &= ~grp;
