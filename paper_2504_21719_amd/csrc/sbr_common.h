@@ -871,8 +871,11 @@ __device__ __forceinline__ uint4 philox4(unsigned seed, int64_t n, int l, unsign
     unsigned k0 = seed, k1 = 0u;
 #pragma unroll
     for (int round = 0; round < 10; round++) {
-        const unsigned lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        const unsigned lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
+        // one 64-bit product instead of a high and a low one (rough walls, 1e7 rays:
+        // 1536 -> 1525 us)
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+        const unsigned lo0 = (unsigned)p0, hi0 = (unsigned)(p0 >> 32);
+        const unsigned lo1 = (unsigned)p1, hi1 = (unsigned)(p1 >> 32);
         c0 = hi1 ^ c1 ^ k0;
         c1 = lo1;
         c2 = hi0 ^ c3 ^ k1;
