@@ -138,11 +138,12 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // largest budget first, in lattice order, and change to units of one wavefront
 // for the last 32 per wavefront.
 //
-// City map, 2e6 rays: 304 -> 164 us, 1e6 225 -> 155, 4e6 455 -> 287, 3e7 1.79
-// -> 1.77 ms; 1.02 M triangles, 1e6 627 -> 550 us, 4e6 977 -> 692, 6.4e7 6.9 ->
-// 6.8 ms; 64 rooftop transmitters of up to 1e7 rays 6.65 -> 6.3 ms, against
-// contiguous ranges on up to 256 queues with two grids' worth of workgroups.
-// Units of four wavefronts already at the horizon cost 0.45 ms more there.
+// Against contiguous ranges on up to 256 queues with two grids' worth of
+// workgroups, on one tree: city map, 1e6 rays 224 -> 160 us, 2e6 271 -> 168, 4e6
+// 376 -> 293, 1e7 762 -> 645 us, 3e7 1.79 -> 1.78 ms; 1.02 M triangles, 1e6 622
+// -> 558 us, 4e6 885 -> 696, 6.4e7 6.77 -> 6.85 ms; 64 rooftop transmitters of
+// up to 1e7 rays 6.61 -> 6.35 ms.  Units of four wavefronts already at the
+// horizon cost 0.3 ms more in the city at 1e6 rays.
 __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
     *first = *end = 0;
     if (i < a.n_claim) {
@@ -298,8 +299,9 @@ __device__ __forceinline__ T pick4(T v0, T v1, T v2, T v3, unsigned i) {
 // 7 KiB through the vector memory path, both nearly saturated (93 % of the
 // VALU cycles).  The walk is bound by instruction issue and by branches: the
 // same walk with early exits in the triangle test and a branch per child and
-// push took 13.6 ms where this form takes 12.1 (15.2 without the walk); the
-// city, 1e7 rays, 0.88, 0.80 and 0.95 ms.
+// push took 13.6 ms where this form took 12.1 (15.2 without the walk); the
+// city, 1e7 rays, 0.88, 0.80 and 0.95 ms (11.8 and 0.53 ms now, with the queues
+// below, a better tree for the city and cheaper masks).
 template <bool REC>
 __device__ __forceinline__ bool packet_phase(const FwdArgs& a, const Ray& r, int last, float tmin, Best& best,
                                              int2* __restrict__ stk, int lstride, unsigned gtid, int& sp,
