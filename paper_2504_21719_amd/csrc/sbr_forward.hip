@@ -72,7 +72,10 @@ struct FwdArgs {
     int once;                      // 1: every wavefront has at most one unit, its own
     int width;                     // rays a wavefront starts at once, on its first lanes
     int claim;                     // work indices per unit
-    unsigned n_claim;              // entries of a queue that are such units; the rest are of `width`
+    int first_width;               // width of a wavefront's first unit
+    unsigned n_first;              // leading entries of a queue that hold the indices [hole, hole + hole_size),
+    int64_t hole, hole_size;       // first_width each
+    unsigned n_claim;              // then, units of `claim`; the rest are of `width`
     unsigned run, n_run;           // consecutive units per queue turn, among the first n_run entries
     // early termination (kernel variant EXT): before segments l >= rr_depth
     int rr_depth;
@@ -144,8 +147,20 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // -> 558 us, 4e6 885 -> 696, 6.4e7 6.77 -> 6.85 ms; 64 rooftop transmitters of
 // up to 1e7 rays 6.61 -> 6.35 ms.  Units of four wavefronts already at the
 // horizon cost 0.3 ms more in the city at 1e6 rays.
+//
+// Where the tree is larger than an L2 (4 MB) a fetch takes longer and so do
+// the wavefronts at the horizon: in calls of up to six units per wavefront the
+// first units, nearest the equator, are then of 16 rays (1.02 M triangles, 4e5
+// rays 501 -> 376 us, 1e6 547 -> 477, 4e6 would take 8 % more; the city would
+// at 1e6 rays too, its fetches being short).
 __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
     *first = *end = 0;
+    if (i < a.n_first) {
+        *first = a.hole + ((int64_t)i * a.nq + q) * a.first_width;
+        *end = *first + a.first_width;
+        return;
+    }
+    i -= a.n_first;
     if (i < a.n_claim) {
         int64_t u = (int64_t)i * a.nq + q;
         if (i < a.n_run) {
@@ -159,6 +174,7 @@ __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q,
             u = u < both ? ((u & 1) ? a.mid + v : a.mid - 1 - v) : (a.mid > above ? a.n_units - 1 - u : u);
         }
         *first = u * a.claim;
+        if (*first >= a.hole) *first += a.hole_size;
         *end = min(a.n_work, *first + a.claim);
     } else {
         const int64_t f = (int64_t)a.n_claim * a.nq * a.claim + ((int64_t)(i - a.n_claim) * a.nq + q) * a.width;
@@ -639,6 +655,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
     // workgroups that share an XCD) and first entry
     int q = 0;
     int looks = 0;                     // at the mask of drained queues
+    int width = kernel_args().first_width;
     int64_t res_b = 0, res_e = 0;      // claimed work indices, not yet started
     {
         const FwdArgs& a = kernel_args();
@@ -679,7 +696,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
         // lane
         if (!exhausted || res_b < res_e) {
             const FwdArgs& a = kernel_args();
-            const unsigned long long own = ~0ull >> (64 - a.width);
+            const unsigned long long own = ~0ull >> (64 - width);
             const unsigned long long need = ballot(!active) & own;
             if (need && (__popcll(need) >= a.refill || need == own)) {
                 const unsigned cnt = (unsigned)__popcll(need);
@@ -713,9 +730,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
                 const int64_t n1 = e1 - b1;
                 const int64_t take1 = min((int64_t)cnt, n1);
                 const int64_t take2 = min((int64_t)cnt - take1, e2 - b2);
+                width = a.width;
                 res_b = take1 < n1 ? b1 + take1 : b2 + take2;
                 res_e = take1 < n1 ? e1 : e2;
-                if (!active && lane < a.width) {
+                if (!active && lane < width) {
                     const unsigned rank = __builtin_amdgcn_mbcnt_hi((unsigned)(need >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((unsigned)need, 0u));
                     const bool mine = rank < (unsigned)(take1 + take2);
@@ -1123,6 +1141,9 @@ static void base_args(FwdArgs& a, const rt_scene* s, int block, const float* eps
     a.refill = 1;
 }
 
+// 4-wide nodes of a tree that fills an L2 of 4 MB.
+static constexpr int64_t kLargeTree = 32768;
+
 // Grid, work queues and spill area of one launch of a.n_work rays.
 static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const LaunchOrder& order, int* blocks_out) {
     const int per_block = block / 64;
@@ -1138,6 +1159,7 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
     a.nq = 1;
     a.run = 1;
     a.claim = a.width;
+    a.first_width = a.width;
     if (a.once) {
         blocks = std::max<int64_t>(1, ((a.n_units + 7) / 8 * 8 + per_block - 1) / per_block);
     } else {
@@ -1161,14 +1183,25 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
             a.n_units = (a.n_work + a.claim - 1) / a.claim;
             const int64_t equator = a.n_tx == 1 ? a.n_work / 2 : a.tx.n_rays / 2 - a.ray_begin;
             a.mid = std::min(a.n_units, std::max<int64_t>(0, equator / a.claim));
+            // narrow first units, a whole number of the others on both sides of mid
+            const int64_t hole = 16 * waves, side = hole / 2 / a.claim;
+            if (s->n_wide >= kLargeTree && a.n_units <= 6 * waves * a.width / a.claim && blocks % a.nq == 0 &&
+                hole % (2 * a.claim) == 0 && a.mid >= side && a.n_units - a.mid > side) {
+                a.first_width = 16;
+                a.n_first = (unsigned)(waves / a.nq);
+                a.mid -= side;
+                a.n_units -= 2 * side;
+                a.hole = a.mid * a.claim;
+                a.hole_size = hole;
+            }
             a.run = (unsigned)std::max<int64_t>(1, rt_order_chunk(order) / (2 * a.claim * a.nq));
         }
     }
     a.n_claim = (unsigned)((a.n_units + a.nq - 1) / a.nq);
     // whole turns of every queue, so that the rest is a stretch of its own
     a.n_run = (unsigned)(a.n_units / ((int64_t)a.run * a.nq)) * a.run;
-    const int64_t rest = std::max<int64_t>(0, a.n_work - (int64_t)a.n_claim * a.nq * a.claim);
-    a.per_queue = a.n_claim + (unsigned long long)((rest + (int64_t)a.width * a.nq - 1) / ((int64_t)a.width * a.nq));
+    const int64_t rest = std::max<int64_t>(0, a.n_work - a.hole_size - (int64_t)a.n_claim * a.nq * a.claim);
+    a.per_queue = (unsigned long long)a.n_first + a.n_claim + (unsigned long long)((rest + (int64_t)a.width * a.nq - 1) / ((int64_t)a.width * a.nq));
     const int64_t threads = blocks * block;
     // a wide traversal pushes up to 3 entries per wide level (= 2 binary levels)
     int64_t need_depth = std::max<int64_t>(0, rt_stack_need(s) - RT_STACK_LDS);

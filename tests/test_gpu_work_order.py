@@ -70,3 +70,31 @@ def test_batched_maps_are_the_single_ones(budgets):
         # a cell before, m^(1/2) 2^-24 (2.6e-6) as they fall; a lost or doubled
         # unit of 64 rays changes a whole cell
         np.testing.assert_allclose(a, b, rtol=2e-5, atol=2e-6 * float(b.max()))
+
+
+@pytest.mark.parametrize("lattice,first,last", [(LANES - 447, 0, LANES - 447), (LANES + 1, 0, LANES + 1),
+                                                (3 * LANES + 77, 0, 3 * LANES + 77), (6 * LANES, 0, 6 * LANES),
+                                                (6 * LANES + 1, 0, 6 * LANES + 1), (4 * LANES, LANES + 99, 4 * LANES),
+                                                (4 * LANES, 2 * LANES - 32768, 4 * LANES - 5),
+                                                (4 * LANES, 2 * LANES - 32700, 4 * LANES - 5),
+                                                (4 * LANES, 0, 2 * LANES + 32768 + 64)])
+def test_every_ray_once_on_a_large_tree(large_scene, lattice, first, last):
+    """First units of 16 rays at the equator, up to six units per wavefront and
+    with room on both sides of it."""
+    rt, torch, cfg, scene, eps, sig = large_scene
+    p = sg.Params(3.5e9, lattice, 0, ray_begin=first, ray_end=last)
+    hits = torch.full((last - first, 1), -7, dtype=torch.int32, device="cuda")
+    stats = torch.zeros(8, dtype=torch.int64, device="cuda")
+    out = torch.empty((1, cfg.plane.H, cfg.plane.W), dtype=torch.float32, device="cuda")
+    rt.rt_radio_map(scene, eps, sig, cfg.tx, cfg.plane, p, out, hits=hits, stats=stats)
+    assert not bool((hits == -7).any()) and not bool((hits == -2).any()), "a ray was not traced"
+    assert int(stats[0]) == last - first
+
+
+@pytest.fixture(scope="module")
+def large_scene():
+    import torch
+    import paper_2504_21719_amd as rt
+    cfg = sg.large_config(1000)
+    t = lambda a: torch.tensor(np.asarray(a), dtype=torch.float32, device="cuda")
+    return rt, torch, cfg, rt.scene_from_mesh(cfg.scene), t(cfg.scene.eps_r), t(cfg.scene.sigma)
