@@ -150,9 +150,9 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 //
 // Where the tree is larger than an L2 (4 MB) a fetch takes longer and so do
 // the wavefronts at the horizon: in calls of up to six units per wavefront the
-// first units, nearest the equator, are then of 16 rays (1.02 M triangles, 4e5
-// rays 501 -> 376 us, 1e6 547 -> 477, 4e6 would take 8 % more; the city would
-// at 1e6 rays too, its fetches being short).
+// first units, nearest the equator, are then of 16 rays (1.02 M triangles, 9e4
+// rays 416 -> 378 us, 2e5 554 -> 397, 4e5 501 -> 376, 1e6 547 -> 477, 4e6 would
+// take 8 % more; the city would at 1e6 rays too, its fetches being short).
 __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
     *first = *end = 0;
     if (i < a.n_first) {
@@ -1154,7 +1154,12 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
     a.width = 64;
     while (a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
     a.n_units = (a.n_work + a.width - 1) / a.width;
-    a.once = (a.n_units + 7) / 8 * 8 <= waves;
+    // one transmitter on a large tree, with room for narrow first units on both
+    // sides of the equator
+    const int64_t equator = a.n_tx == 1 ? a.n_work / 2 : a.tx.n_rays / 2 - a.ray_begin;
+    const bool narrow_first = a.n_tx <= 1 && s->n_wide >= kLargeTree && equator > 8 * waves + 256 &&
+                              a.n_work - equator > 8 * waves + 256;
+    a.once = (a.n_units + 7) / 8 * 8 <= waves && !(narrow_first && a.width > 16);
     a.mid = -1;
     a.nq = 1;
     a.run = 1;
@@ -1181,11 +1186,10 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
             a.n_units = std::max<int64_t>(0, a.n_work - narrow) / a.claim / a.nq * a.nq;
         } else {
             a.n_units = (a.n_work + a.claim - 1) / a.claim;
-            const int64_t equator = a.n_tx == 1 ? a.n_work / 2 : a.tx.n_rays / 2 - a.ray_begin;
             a.mid = std::min(a.n_units, std::max<int64_t>(0, equator / a.claim));
             // narrow first units, a whole number of the others on both sides of mid
             const int64_t hole = 16 * waves, side = hole / 2 / a.claim;
-            if (s->n_wide >= kLargeTree && a.n_units <= 6 * waves * a.width / a.claim && blocks % a.nq == 0 &&
+            if (narrow_first && a.n_units <= 6 * waves * 64 / a.claim && blocks % a.nq == 0 &&
                 hole % (2 * a.claim) == 0 && a.mid >= side && a.n_units - a.mid > side) {
                 a.first_width = 16;
                 a.n_first = (unsigned)(waves / a.nq);

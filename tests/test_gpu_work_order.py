@@ -72,7 +72,11 @@ def test_batched_maps_are_the_single_ones(budgets):
         np.testing.assert_allclose(a, b, rtol=2e-5, atol=2e-6 * float(b.max()))
 
 
-@pytest.mark.parametrize("lattice,first,last", [(LANES - 447, 0, LANES - 447), (LANES + 1, 0, LANES + 1),
+@pytest.mark.parametrize("lattice,first,last", [(LANES // 4, 0, LANES // 4), (LANES // 4 + 513, 0, LANES // 4 + 513),
+                                                (LANES // 4 + 700, 0, LANES // 4 + 700),
+                                                (LANES // 2 + 9, 0, LANES // 2 + 9), (LANES, 300, LANES - 5),
+                                                (LANES, LANES // 2 - 100, LANES - 5), (LANES, 0, LANES // 2 + 100),
+                                                (LANES - 447, 0, LANES - 447), (LANES + 1, 0, LANES + 1),
                                                 (3 * LANES + 77, 0, 3 * LANES + 77), (6 * LANES, 0, 6 * LANES),
                                                 (6 * LANES + 1, 0, 6 * LANES + 1), (4 * LANES, LANES + 99, 4 * LANES),
                                                 (4 * LANES, 2 * LANES - 32768, 4 * LANES - 5),
