@@ -188,6 +188,10 @@ static rt_status check_params(const rt_sbr_params* p, int64_t* b, int64_t* e) {
     return RT_OK;
 }
 
+// -0 becomes +0: the traversal orders entry distances, t_min at least, by their
+// bits, where -0 would come last.
+static float plus_zero(float t_min) { return t_min + 0.0f; }
+
 static void fill_plane(const rt_plane* p, double freq, PlaneDesc* d) {
     d->z = (float)p->z;
     d->x0 = (float)p->x0;
@@ -340,7 +344,7 @@ extern "C" rt_status rt_radio_map(const rt_scene* scene, rt_materials materials,
     f.ray_begin = b;
     f.ray_end = e;
     f.L = params->max_depth;
-    f.t_min = params->t_min;
+    f.t_min = plus_zero(params->t_min);
     f.accel = params->accel;
     f.deposit = pick_deposit(scene, params);
     f.block = pick_block(scene, params);
@@ -587,7 +591,7 @@ extern "C" rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials ma
     bl.total_waves = hw[n_tx];
     fill_plane(plane, params->freq_hz, &bl.pl);
     bl.L = params->max_depth;
-    bl.t_min = params->t_min;
+    bl.t_min = plus_zero(params->t_min);
     bl.block = pick_block(scene, params);
     bl.deposit = pick_deposit(scene, params);
     bl.refill = pick_refill(scene);
