@@ -367,12 +367,14 @@ __device__ __forceinline__ float safe_inv(float d) {
     return __builtin_amdgcn_rcpf(a);
 }
 
-// At most a b: the rounded product c lies within half an ulp of a b, and
-// |c| 2^-24 is between half an ulp and one, so c lowered by it and rounded is
-// c's lower neighbour (or c minus half an ulp of it at a power of two).
+// At most a b, where the product does not underflow: the rounded product c lies
+// within half an ulp of a b, and 1.5 |c| 2^-24 is between 3/4 of an ulp and 3/2,
+// so c lowered by it and rounded is below c by an ulp (of the magnitude under it,
+// at a positive power of two by two of those).  (Without the 1.5 the difference
+// is a tie at a negative power of two, and rounds back to c.)
 __device__ __forceinline__ float mul_down(float a, float b) {
     const float c = a * b;
-    return __builtin_fmaf(fabsf(c), -0x1p-24f, c);
+    return __builtin_fmaf(fabsf(c), -0x1.8p-24f, c);
 }
 
 __device__ __forceinline__ void ray_setup(Ray& r) {
@@ -398,14 +400,13 @@ __device__ __forceinline__ void ray_setup(Ray& r) {
     r.jx = r.ix * kBoxSlack;
     r.jy = r.iy * kBoxSlack;
     r.jz = r.iz * kBoxSlack;
-    // planes are evaluated as one fma, p i + cn and p j + cf, with cn the
-    // product -o i rounded down and cf the product -o j rounded up (directed
-    // by its exact residual): p i + cn never exceeds (p - o) i and p j + cf
-    // never falls below (p - o) j, but for the fma's own rounding, which is
-    // relative and covered by kBoxSlack, so no box is culled that the exact
-    // test keeps.  The widening is at most one ulp of o i: lowering and
-    // raising by 2^-22 |o i| instead let a ray enter the boxes of the
-    // neighbours that its origin touches from behind.
+    // planes are evaluated as one fma, p i + cn and p j + cf, with cn at most
+    // the product -o i and cf at least the product -o j (mul_down): p i + cn
+    // never exceeds (p - o) i and p j + cf never falls below (p - o) j, but for
+    // the fma's own rounding, which is relative and covered by kBoxSlack, so no
+    // box is culled that the exact test keeps.  The widening is at most an ulp
+    // and a half of o i: lowering and raising by 2^-22 |o i| instead let a ray
+    // enter the boxes of the neighbours that its origin touches from behind.
     r.cnx = mul_down(-r.ox, r.ix);
     r.cny = mul_down(-r.oy, r.iy);
     r.cnz = mul_down(-r.oz, r.iz);
