@@ -1181,6 +1181,8 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
         a.claim = 64 * (int)std::max<int64_t>(1, std::min<int64_t>(4, a.n_units / (waves * 16)));
         if (const char* env = getenv("RTMAP_CLAIM"))
             a.claim = std::max(64, std::min(4096, atoi(env)));
+        // entries are numbered in 32 bits
+        while (a.n_work / a.claim / a.nq >= (int64_t)1 << 30) a.claim *= 2;
         const int64_t narrow = a.n_tx > 1 ? 32 * waves * a.width : 0;     // indices left to units of one wavefront
         if (a.n_tx > 1) {
             a.n_units = std::max<int64_t>(0, a.n_work - narrow) / a.claim / a.nq * a.nq;
