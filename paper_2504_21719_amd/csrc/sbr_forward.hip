@@ -1145,14 +1145,17 @@ static void base_args(FwdArgs& a, const rt_scene* s, int block, const float* eps
 static constexpr int64_t kLargeTree = 32768;
 
 // Grid, work queues and spill area of one launch of a.n_work rays.
-static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const LaunchOrder& order, int* blocks_out) {
+static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const LaunchOrder& order, bool brute,
+                             int* blocks_out) {
     const int per_block = block / 64;
     int64_t blocks = rt_persistent_blocks(block, s->device);
     int64_t waves = blocks * per_block;
     // fewer rays than the resident wavefronts have lanes: narrower wavefronts
-    // (whose lanes wait less for each other), at least 8 rays wide
+    // (whose lanes wait less for each other), at least 8 rays wide; not where
+    // every triangle is tested, for as long on each lane (5,810 triangles, 2e4
+    // rays: 11.4 ms with 8 rays per wavefront, 8.6 with 64)
     a.width = 64;
-    while (a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
+    while (!brute && a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
     a.n_units = (a.n_work + a.width - 1) / a.width;
     // one transmitter on a large tree, with room for narrow first units on both
     // sides of the equator
@@ -1284,7 +1287,7 @@ rt_status rt_launch_forward(const FwdLaunch& f, hipStream_t st) {
     a.stats = f.stats;
     a.refill = std::max(1, std::min(64, f.refill));
     int blocks = 0;
-    rt_status r = size_launch(a, s, f.block, f.tx.order, &blocks);
+    rt_status r = size_launch(a, s, f.block, f.tx.order, f.accel == RT_ACCEL_BRUTE, &blocks);
     if (r != RT_OK) return r;
     int64_t map_n = a.map_stride * a.npol;
     {
@@ -1340,7 +1343,7 @@ rt_status rt_launch_forward_multi(const rt_scene* s, const float* eps_r, const f
         a.tape_groups = 2;
     }
     int blocks = 0;
-    rt_status r = size_launch(a, s, block, order, &blocks);
+    rt_status r = size_launch(a, s, block, order, false, &blocks);
     if (r != RT_OK) return r;
     int g = (int)std::min<int64_t>(4096, std::max<int64_t>(2, (zero_floats + 255) / 256));
     hipLaunchKernelGGL(k_prepare, dim3(g), dim3(256), 0, st, maps, zero_floats, s->counters, a.nq,

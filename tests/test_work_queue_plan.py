@@ -84,7 +84,7 @@ def lib(tmp_path_factory):
     parts = [re.search(p, src, re.S).group(0) for p in
              (r"struct FwdArgs \{.*?\n\};\n", r"__device__ __forceinline__ void queue_entry\(.*?\n\}\n",
               r"static constexpr int64_t kLargeTree[^\n]*;\n", r"static rt_status size_launch\(.*?\n\}\n")]
-    call = "size_launch(a, &s, c->block, order, &blocks)"
+    call = "size_launch(a, &s, c->block, order, c->brute != 0, &blocks)"
     d = tmp_path_factory.mktemp("queues")
     cpp, so = str(d / "q.cpp"), str(d / "q.so")
     head, harness = HARNESS.split("static FwdArgs g_args;")
@@ -161,3 +161,10 @@ def test_largest_calls(lib, monkeypatch, n, n_tx, queues, claim):
     got = np.array(sorted(got))
     assert len(got) > 5000 and got[0, 0] >= 0 and got[-1, 1] <= n
     assert np.all(got[1:, 0] >= got[:-1, 1])
+
+
+@pytest.mark.parametrize("n", [1, 100, 20_000, 100_000])
+def test_brute_force_keeps_whole_wavefronts(lib, n):
+    """Each narrow wavefront would test all triangles for its few rays."""
+    assert _plan(lib, n, brute=1).width == 64
+    assert _plan(lib, n).width < 64
