@@ -102,6 +102,10 @@ struct FwdArgs {
     const int32_t* slots;    // output slot of each ordered transmitter
     int n_tx;
     int64_t slot_stride;     // floats between the maps of consecutive slots
+    // unit of entry i = r run + k of queue q, i < n_run: r by_r + k by_k + q by_q (runs of units per queue and turn:
+    // nq run, 1 and run; or `run` stretches per queue in turn: 1, and nq and 1 times their length).  Down here:
+    // further up these took the others off the boundaries that wide scalar loads need (0.5 %)
+    unsigned by_r, by_k, by_q;
 };
 
 // Kernel modes: one transmitter; several transmitters with one material set
@@ -148,6 +152,18 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // up to 1e7 rays 6.61 -> 6.35 ms.  Units of four wavefronts already at the
 // horizon cost 0.3 ms more in the city at 1e6 rays.
 //
+// One front also brings the deposits together in the few cells under it.  Where
+// a wavefront does not sum them first (one atomic per crossing, or a launch in
+// lattice order, whose wavefronts hold no neighbours), calls of four units per
+// wavefront and more go through several stretches at once instead, one per
+// queue and turn (against one front, and in brackets the contiguous ranges on 256
+// queues; city: lattice order, 5e6 rays 1.60 -> 1.14 ms [1.23], 2e7 6.5 -> 4.5
+// [4.5]; atomics, 2e6 0.55 -> 0.45 [0.48], 5e6 1.57 -> 1.20 [1.20], 2e7 5.6 -> 4.7
+// [5.6]; three transmitters of 3e6 rays 3.9 -> 1.9 [2.1] and 4.4 -> 2.8 [3.5]).
+// Few stretches suffice in lattice order, where the 1.02 M-triangle scene would
+// lose 10 % at 1.5e6 rays with 16; atomics take 16 (with 4 the city's 1.1e6 rays
+// take 0.33 ms, with 16 0.27).
+//
 // Where the tree is larger than an L2 (4 MB) a fetch takes longer and so do
 // the wavefronts at the horizon: in calls of up to six units per wavefront the
 // first units, nearest the equator, are then of 16 rays (1.02 M triangles, 9e4
@@ -162,18 +178,21 @@ __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q,
     }
     i -= a.n_first;
     if (i < a.n_claim) {
-        int64_t u = (int64_t)i * a.nq + q;
+        // units are numbered in 32 bits
+        const unsigned n_units = (unsigned)a.n_units;
+        const int mid = (int)a.mid;
+        unsigned u = i * (unsigned)a.nq + (unsigned)q;
         if (i < a.n_run) {
-            const unsigned r = i / a.run;
-            u = ((int64_t)r * a.nq + q) * a.run + (i - r * a.run);
+            const unsigned r = i / a.run, k = i - r * a.run;
+            u = r * a.by_r + k * a.by_k + (unsigned)q * a.by_q;
         }
-        if (u >= a.n_units) return;
-        if (a.mid >= 0) {
+        if (u >= n_units) return;
+        if (mid >= 0) {
             // outward from mid: the two sides in turn, then the rest of the longer one
-            const int64_t above = a.n_units - a.mid, both = 2 * min(a.mid, above), v = u >> 1;
-            u = u < both ? ((u & 1) ? a.mid + v : a.mid - 1 - v) : (a.mid > above ? a.n_units - 1 - u : u);
+            const unsigned below = (unsigned)mid, above = n_units - below, both = 2u * min(below, above), v = u >> 1;
+            u = u < both ? ((u & 1u) ? below + v : below - 1u - v) : (below > above ? n_units - 1u - u : u);
         }
-        *first = u * a.claim;
+        *first = (int64_t)u * a.claim;
         if (*first >= a.hole) *first += a.hole_size;
         *end = min(a.n_work, *first + a.claim);
     } else {
@@ -1168,6 +1187,8 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
     a.run = 1;
     a.claim = a.width;
     a.first_width = a.width;
+    unsigned n_stretch = 0;        // stretches per queue that come in turn, 0 = one front
+    int64_t stretch = 0;           // units in each
     if (a.once) {
         blocks = std::max<int64_t>(1, ((a.n_units + 7) / 8 * 8 + per_block - 1) / per_block);
     } else {
@@ -1184,11 +1205,18 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
         a.claim = 64 * (int)std::max<int64_t>(1, std::min<int64_t>(4, a.n_units / (waves * 16)));
         if (const char* env = getenv("RTMAP_CLAIM"))
             a.claim = std::max(64, std::min(4096, atoi(env)));
-        // entries are numbered in 32 bits
-        while (a.n_work / a.claim / a.nq >= (int64_t)1 << 30) a.claim *= 2;
-        const int64_t narrow = a.n_tx > 1 ? 32 * waves * a.width : 0;     // indices left to units of one wavefront
+        // units, and so entries, are numbered in 32 bits
+        while (a.n_work / a.claim >= (int64_t)1 << 30) a.claim *= 2;
+        // stretches in turn (see queue_entry) where deposits would meet, but for a
+        // geometry tape, which takes none
+        if (a.tape_groups == 4 && a.n_units >= 4 * waves) {
+            if (a.deposit == RT_DEPOSIT_ATOMIC) n_stretch = 16;
+            else if (order.chunk == 0) n_stretch = a.n_tx > 0 ? 8 : 1;
+        }
+        const int64_t turn = (int64_t)a.nq * std::max(1u, n_stretch);
+        const int64_t narrow = a.n_tx > 1 && !n_stretch ? 32 * waves * a.width : 0;     // indices left to units of one wavefront
         if (a.n_tx > 1) {
-            a.n_units = std::max<int64_t>(0, a.n_work - narrow) / a.claim / a.nq * a.nq;
+            a.n_units = std::max<int64_t>(0, a.n_work - narrow) / a.claim / turn * turn;
         } else {
             a.n_units = (a.n_work + a.claim - 1) / a.claim;
             a.mid = std::min(a.n_units, std::max<int64_t>(0, equator / a.claim));
@@ -1205,10 +1233,22 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
             }
             a.run = (unsigned)std::max<int64_t>(1, rt_order_chunk(order) / (2 * a.claim * a.nq));
         }
+        stretch = (a.n_units + turn - 1) / turn;
     }
-    a.n_claim = (unsigned)((a.n_units + a.nq - 1) / a.nq);
-    // whole turns of every queue, so that the rest is a stretch of its own
-    a.n_run = (unsigned)(a.n_units / ((int64_t)a.run * a.nq)) * a.run;
+    if (n_stretch) {
+        a.run = n_stretch;
+        a.n_claim = a.n_run = (unsigned)(n_stretch * stretch);
+        a.by_r = 1;
+        a.by_k = (unsigned)(a.nq * stretch);
+        a.by_q = (unsigned)stretch;
+    } else {
+        a.n_claim = (unsigned)((a.n_units + a.nq - 1) / a.nq);
+        // whole turns of every queue, so that the rest is a stretch of its own
+        a.n_run = (unsigned)(a.n_units / ((int64_t)a.run * a.nq)) * a.run;
+        a.by_r = (unsigned)a.nq * a.run;
+        a.by_k = 1;
+        a.by_q = a.run;
+    }
     const int64_t rest = std::max<int64_t>(0, a.n_work - a.hole_size - (int64_t)a.n_claim * a.nq * a.claim);
     a.per_queue = (unsigned long long)a.n_first + a.n_claim + (unsigned long long)((rest + (int64_t)a.width * a.nq - 1) / ((int64_t)a.width * a.nq));
     const int64_t threads = blocks * block;

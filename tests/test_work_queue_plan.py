@@ -54,6 +54,7 @@ extern "C" int plan(Call* c) {
     c->per_queue = (int64_t)a.per_queue;
     c->n_first = a.n_first;
     c->first_width = a.first_width;
+    c->spread = a.by_r == 1 && a.by_k != 1 ? a.run : 0;
     return st;
 }
 // work of entry i of queue q, of the last plan
@@ -143,7 +144,7 @@ def test_largest_calls(lib, monkeypatch, n, n_tx, queues, claim):
         monkeypatch.setenv("RTMAP_QUEUES", queues)
         monkeypatch.setenv("RTMAP_CLAIM", claim)
     c = _plan(lib, n, n_tx=n_tx)
-    assert c.per_queue < 2 ** 32
+    assert c.per_queue < 2 ** 32 and c.n_claim * c.nq < 2 ** 32
     assert c.n_claim * c.nq >= c.n_units
     rest = n - c.n_claim * c.nq * c.claim
     assert (c.per_queue - c.n_claim) * c.nq * c.width >= rest
@@ -168,3 +169,25 @@ def test_brute_force_keeps_whole_wavefronts(lib, n):
     """Each narrow wavefront would test all triangles for its few rays."""
     assert _plan(lib, n, brute=1).width == 64
     assert _plan(lib, n).width < 64
+
+
+@pytest.mark.parametrize("n_tx", [0, 1, 3])
+@pytest.mark.parametrize("queues,claim", [(None, None), ("1", "64"), ("7", "192"), ("32", "4096")])
+def test_stretches(lib, monkeypatch, n_tx, queues, claim):
+    """Calls of many units whose deposits are not summed (atomic strategy, or
+    lattice order) go through stretches in turn, the others along one front."""
+    if queues:
+        monkeypatch.setenv("RTMAP_QUEUES", queues)
+        monkeypatch.setenv("RTMAP_CLAIM", claim)
+    for n in (4 * LANES - 64, 4 * LANES - 63, 5 * LANES + 1, 9 * LANES + 77, 33 * LANES + 17, 70 * LANES + 5):
+        for deposit, chunk in ((1, 987), (2, 1), (1, 1), (2, 987)):
+            for begin, lattice in ((0, n), (n // 3, 2 * n)):
+                for n_wide in (100, 40_000):
+                    c = _plan(lib, n, 4, n_tx=n_tx, chunk=chunk, n_wide=n_wide, begin=begin, lattice=lattice,
+                              deposit=deposit)
+                    if not queues and n_wide == 100:
+                        assert bool(c.spread) == (n > 4 * LANES - 64 and (deposit, chunk) != (2, 987))
+                    _every_index_once(lib, c)
+    if not queues:
+        c = _plan(lib, 2 ** 40, n_tx=n_tx, deposit=1)
+        assert c.spread == 16 and c.per_queue < 2 ** 32 and c.n_claim * c.nq >= c.n_units
