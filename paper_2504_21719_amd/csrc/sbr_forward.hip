@@ -169,6 +169,12 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // first units, nearest the equator, are then of 16 rays (1.02 M triangles, 9e4
 // rays 416 -> 378 us, 2e5 554 -> 397, 4e5 501 -> 376, 1e6 547 -> 477, 4e6 would
 // take 8 % more; the city would at 1e6 rays too, its fetches being short).
+//
+// Several transmitters on such a tree have their horizons one after another, the
+// last near the call's end; in calls of up to 64 units per wavefront in all and
+// 8 per transmitter four stretches per queue spread them (64 transmitters of 5e4
+// rays 1.40 -> 1.10 ms, 16 of 3e5 1.51 -> 1.24, 64 of 2e5 3.74 -> 3.40; larger
+// calls lose: 32 of up to 2e6 rays 6.4 -> 7.4, 3 of 3e6 1.67 -> 1.80).
 __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
     *first = *end = 0;
     if (i < a.n_first) {
@@ -1213,6 +1219,10 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
             if (a.deposit == RT_DEPOSIT_ATOMIC) n_stretch = 16;
             else if (order.chunk == 0) n_stretch = a.n_tx > 0 ? 8 : 1;
         }
+        // and where the transmitters' horizons would follow one another
+        if (!n_stretch && a.n_tx > 1 && s->n_wide >= kLargeTree && a.n_units >= 4 * waves &&
+            a.n_units <= waves * std::min(64, 8 * a.n_tx))
+            n_stretch = 4;
         const int64_t turn = (int64_t)a.nq * std::max(1u, n_stretch);
         const int64_t narrow = a.n_tx > 1 && !n_stretch ? 32 * waves * a.width : 0;     // indices left to units of one wavefront
         if (a.n_tx > 1) {

@@ -191,3 +191,15 @@ def test_stretches(lib, monkeypatch, n_tx, queues, claim):
     if not queues:
         c = _plan(lib, 2 ** 40, n_tx=n_tx, deposit=1)
         assert c.spread == 16 and c.per_queue < 2 ** 32 and c.n_claim * c.nq >= c.n_units
+
+
+@pytest.mark.parametrize("n_tx", [2, 3, 16, 64])
+def test_horizons_of_several_transmitters(lib, n_tx):
+    """On a large tree the transmitters of middling calls go through stretches."""
+    for units in (4, 7, 15, 17, 30, 63, 65):
+        n = units * LANES + 77
+        c = _plan(lib, n, 4, n_tx=n_tx, n_wide=40_000)
+        if n > 2 * 4096 + LANES:                     # some turns of 4 stretches on 16 queues
+            assert (c.spread == 4) == (units < min(64, 8 * n_tx))
+        _every_index_once(lib, c)
+        assert not _plan(lib, n, 4, n_tx=n_tx, n_wide=30_000).spread
