@@ -211,8 +211,8 @@ __global__ void __launch_bounds__(kBlock) k_morton(const float* __restrict__ V, 
 // ---- sort of few triangles --------------------------------------------------
 // One workgroup sorts up to kSortOne pairs in LDS by (code, triangle), a bitonic
 // network: the radix sort's 24 launches take 116 us at any small size, this
-// takes 28 us for the 1202 triangles of the city.
-constexpr int kSortOne = 2048, kSortBlock = 1024;
+// takes 28 us for the 1202 triangles of the city, 54 us for 3890.
+constexpr int kSortOne = 4096, kSortBlock = 1024;
 __global__ void __launch_bounds__(kSortBlock) k_sort_one(uint64_t* __restrict__ keys, uint32_t* __restrict__ vals, int n) {
     __shared__ uint64_t k[kSortOne];
     __shared__ uint32_t v[kSortOne];
@@ -648,11 +648,10 @@ __device__ __forceinline__ int wide_children(const float4* __restrict__ nodes, i
 // to a single house's: on the city (1202 triangles, ground of 2) a segment
 // visits 7.5 wide nodes of the Karras tree and 5.0 of this one.  Maps of 1e6 and
 // 1e7 rays 162 -> 135 and 618 -> 539 us, 64 rooftop transmitters 6.3 -> 5.3 ms;
-// the build 306 -> 435 us, of which k_sah_top 137 and k_sah_small 86 us (serial:
-// one wavefront per node and level).  Larger scenes are left out because one
-// workgroup makes the upper splits (at 4096 triangles it takes what a map of
-// 1e6 rays gains, at 8192 twice that), and for what it would give them: 9 % of the
-// visits on the 1.02 M-triangle terrain, whose triangles are alike.
+// in the build k_sah_top takes 127 and k_sah_small 59 us.  Larger scenes are
+// left out because one workgroup makes the upper splits: at 3890 triangles the two
+// take 350 us, twice what a map of 1e6 rays gains.  The 1.02 M-triangle terrain,
+// whose triangles are alike, would be visited 9 % less.
 //
 // Node numbers are those of a depth-first walk: the left child of node i is
 // i + 1, the right one i + (leaves on the left); triangle order within a node
@@ -722,19 +721,49 @@ __device__ __forceinline__ void node_store(float4* __restrict__ nodes, int i, co
     nodes[4 * (int64_t)i + 3] = make_float4(__int_as_float(left), __int_as_float(right), 0.0f, 0.0f);
 }
 
-// Splits every node of more than kSahSmall triangles, level by level, one
-// wavefront per node: bounds of the centres, kSahBins bins per axis, the best
-// of the 3 (kSahBins - 1) planes (one per lane), a stable partition.  A task is
-// {first, end, node, -}; those left for k_sah_small are {first, end, node, which
-// of the two buffers}.  At the end, the depth of the Karras tree `karras`,
-// by doubling the parent links.
+// Least and greatest of a wavefront's values, on every lane: data-parallel
+// primitives (rows of 16 by shifts, then across the rows).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_or(float v, float none) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+template <typename F>
+__device__ __forceinline__ float wave_fold(float v, float none, F f) {
+    v = f(v, dpp_or<0x111, 0xf>(v, none));
+    v = f(v, dpp_or<0x112, 0xf>(v, none));
+    v = f(v, dpp_or<0x114, 0xf>(v, none));
+    v = f(v, dpp_or<0x118, 0xf>(v, none));
+    v = f(v, dpp_or<0x142, 0xa>(v, none));
+    v = f(v, dpp_or<0x143, 0xc>(v, none));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ void wave_union(Box& b) {
+    for (int x = 0; x < 3; x++) {
+        b.lo[x] = wave_fold(b.lo[x], INFINITY, [](float p, float q) { return fminf(p, q); });
+        b.hi[x] = wave_fold(b.hi[x], -INFINITY, [](float p, float q) { return fmaxf(p, q); });
+    }
+}
+
+// Splits every node of more than kSahSmall triangles, level by level: bounds of
+// the centres, kSahBins bins per axis, the best of the 3 (kSahBins - 1) planes
+// (one per lane), a stable partition.  A node's triangles are shared out over
+// wavefronts that a level of few nodes leaves idle, each of which chooses the
+// same plane from the common bins.  A level takes 12 us (bound by latency: four
+// rounds of loads, as many barriers) to 35 (the bins' LDS atomics, on which all
+// wavefronts wait): 266 us on 3890 triangles, 189 on 2354 and 127 on 1202; with
+// one wavefront per node, sums by LDS permutes and every extreme an atomic 375,
+// 231 and 136.  A task is {first, end, node, -}; those left for k_sah_small are
+// {first, end, node, which of the two buffers}.  At the end, the depth of the
+// Karras tree `karras`, by doubling the parent links.
 __global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict__ boxes, int n,
                                                        const float4* __restrict__ karras, float4* __restrict__ nodes,
                                                        float4* buf0, float4* buf1, int4* __restrict__ small,
                                                        BuildState* __restrict__ st) {
     __shared__ unsigned bins[kSahWaves][3][kSahBins][7];     // ordered-int lo, hi; count
+    __shared__ float part[kSahWaves][12];                    // a wavefront's bounds, then its boxes of both halves
+    __shared__ int n_lefts[kSahWaves];
     __shared__ int4 list[2][kSahQueue];
-    __shared__ int count[2], n_small;
+    __shared__ int count[2], largest[2], n_small;        // of a level's nodes: number, most triangles
     __shared__ unsigned short par[kSahMax], dep[kSahMax];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < n; i += kSahBlock) {
@@ -746,6 +775,8 @@ __global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict_
         n_small = n <= kSahSmall ? 1 : 0;
         count[0] = 1 - n_small;
         count[1] = 0;
+        largest[0] = n;
+        largest[1] = 0;
         if (n_small) small[0] = make_int4(0, n, 0, 0);
         else list[0][0] = make_int4(0, n, 0, 0);
     }
@@ -753,49 +784,86 @@ __global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict_
     for (int level = 0; count[level & 1] > 0; level++) {
         const float4* in = level & 1 ? buf1 : buf0;
         float4* out = level & 1 ? buf0 : buf1;
-        for (int t = wave; t < count[level & 1]; t += kSahWaves) {
-            const int4 task = list[level & 1][t];
+        const int n_tasks = count[level & 1];
+        // wavefronts per node: 256 triangles are one round of loads for one
+        int g = kSahWaves;
+        while (g > 1 && (n_tasks * g > kSahWaves || largest[level & 1] <= 128 * g)) g >>= 1;
+        // the same number of rounds and barriers for every wavefront
+        auto sync = [&]() {
+            if (g > 1) {
+                __threadfence_block();
+                __syncthreads();
+            } else {
+                wave_fence();
+            }
+        };
+        const int sub = wave & (g - 1), lead = wave - sub;
+        for (int t0 = 0; t0 < n_tasks; t0 += kSahWaves / g) {
+            const bool has = t0 + wave / g < n_tasks;
+            const int4 task = list[level & 1][has ? t0 + wave / g : 0];
             const int lo = task.x, hi = task.y, cnt = hi - lo;
-            unsigned(*const bn)[kSahBins][7] = bins[wave];
+            // this wavefront's triangles (none without a node)
+            const int each = ((cnt + g - 1) / g + 63) & ~63;
+            const int s0 = has ? min(hi, lo + sub * each) : lo, s1 = has ? min(hi, s0 + each) : lo;
+            unsigned(*const bn)[kSahBins][7] = bins[lead];
+            if (sub == 0)
+                for (int i = lane; i < 3 * kSahBins * 7; i += 64) (&bn[0][0][0])[i] = i % 7 < 3 ? 0xffffffffu : 0u;
             Box c = kNoBox;
-            sah_for(in, lo, hi, lane, [&](const SahBox& b, int, bool) {      // the last one again is no harm
+            sah_for(in, s0, s1, lane, [&](const SahBox& b, int, bool) {      // the last one again is no harm
                 for (int a = 0; a < 3; a++) {
                     c.lo[a] = fminf(c.lo[a], box_centre(b.box, a));
                     c.hi[a] = fmaxf(c.hi[a], box_centre(b.box, a));
                 }
             });
+            wave_union(c);
+            if (lane == 0)
+                for (int a = 0; a < 3; a++) {
+                    part[wave][a] = c.lo[a];
+                    part[wave][3 + a] = c.hi[a];
+                }
+            sync();
             float scale[3];
             for (int a = 0; a < 3; a++) {
-                for (int off = 32; off >= 1; off >>= 1) {
-                    c.lo[a] = fminf(c.lo[a], __shfl_xor(c.lo[a], off));
-                    c.hi[a] = fmaxf(c.hi[a], __shfl_xor(c.hi[a], off));
+                for (int w = lead; w < lead + g; w++) {
+                    c.lo[a] = fminf(c.lo[a], part[w][a]);
+                    c.hi[a] = fmaxf(c.hi[a], part[w][3 + a]);
                 }
                 const float ext = c.hi[a] - c.lo[a];
                 scale[a] = ext > 0.0f ? (float)kSahBins / ext : 0.0f;
             }
             auto bin = [&](const Box& b, int a) { return sah_bin(box_centre(b, a), c.lo[a], scale[a]); };
-            for (int i = lane; i < 3 * kSahBins * 7; i += 64) (&bn[0][0][0])[i] = i % 7 < 3 ? 0xffffffffu : 0u;
-            wave_fence();
-            sah_for(in, lo, hi, lane, [&](const SahBox& b, int, bool on) {
+            sah_for(in, s0, s1, lane, [&](const SahBox& b, int, bool on) {
                 if (!on) return;
+                // extremes first read: seldom does one move after the first few, and
+                // reads at one address are one, atomics one per lane
+                unsigned* w[3];
+                unsigned now[3][6], own[6];
+                for (int x = 0; x < 3; x++) {
+                    own[x] = f2ord(b.box.lo[x]);
+                    own[3 + x] = f2ord(b.box.hi[x]);
+                }
                 for (int a = 0; a < 3; a++) {
-                    unsigned* const w = bn[a][bin(b.box, a)];
+                    w[a] = bn[a][bin(b.box, a)];
+                    for (int x = 0; x < 6; x++) now[a][x] = w[a][x];
+                }
+                for (int a = 0; a < 3; a++) {
+                    atomicAdd(w[a] + 6, 1u);
                     for (int x = 0; x < 3; x++) {
-                        atomicMin(w + x, f2ord(b.box.lo[x]));
-                        atomicMax(w + 3 + x, f2ord(b.box.hi[x]));
+                        if (own[x] < now[a][x]) atomicMin(w[a] + x, own[x]);
+                        if (own[3 + x] > now[a][3 + x]) atomicMax(w[a] + 3 + x, own[3 + x]);
                     }
-                    atomicAdd(w + 6, 1u);
                 }
             });
-            wave_fence();
+            sync();
             // lane = axis (kSahBins - 1) + plane
             const int axis = lane < kSahBins - 1 ? 0 : lane < 2 * (kSahBins - 1) ? 1 : 2;
             const int plane = lane - axis * (kSahBins - 1) + 1;
             Box L = kNoBox, R = kNoBox;
             int nl = 0, nr = 0;
+            // (an empty bin's bounds read as NaN, which no minimum or maximum takes)
+#pragma unroll 8
             for (int k = 0; k < kSahBins; k++) {
                 const unsigned* const w = bn[axis][k];
-                if (w[6] == 0u) continue;
                 Box b;
                 for (int x = 0; x < 3; x++) {
                     b.lo[x] = ord2f(w[x]);
@@ -807,23 +875,31 @@ __global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict_
                 nr += k < plane ? 0 : (int)w[6];
             }
             float cost = plane < kSahBins && nl > 0 && nr > 0 ? split_cost(L, nl, R, nr) : INFINITY;
-            int best = lane;
-            for (int off = 32; off >= 1; off >>= 1) {
-                const float c2 = __shfl_xor(cost, off);
-                const int b2 = __shfl_xor(best, off);
-                if (c2 < cost || (c2 == cost && b2 < best)) {
-                    cost = c2;
-                    best = b2;
-                }
-            }
-            const bool halves = !(cost < INFINITY) || level >= kSahDeep;
+            // the first lane of the least cost
+            const float least = wave_fold(cost, INFINITY, [](float p, float q) { return fminf(p, q); });
+            const int best = __builtin_ctzll(__ballot(cost == least));
+            const bool halves = !(least < INFINITY) || level >= kSahDeep;
             const int ax = __shfl(axis, best), pl = __shfl(plane, best);
             const int n_left = halves ? cnt / 2 : __shfl(nl, best);
-            L = R = kNoBox;
-            int done_l = 0, done_r = 0;
-            sah_for(in, lo, hi, lane, [&](const SahBox& b, int i, bool on) {
+            auto goes_left = [&](const SahBox& b, int i) {
                 const int side = ax == 0 ? bin(b.box, 0) : ax == 1 ? bin(b.box, 1) : bin(b.box, 2);
-                const bool left = on && (halves ? i < lo + n_left : side < pl);
+                return halves ? i < lo + n_left : side < pl;
+            };
+            // those that go left before this wavefront's first
+            int done_l = 0;
+            if (g > 1) {
+                int mine = 0;
+                sah_for(in, s0, s1, lane, [&](const SahBox& b, int i, bool on) {
+                    mine += (int)__popcll(__ballot(on && goes_left(b, i)));
+                });
+                if (lane == 0) n_lefts[wave] = mine;
+                sync();
+                for (int w = lead; w < wave; w++) done_l += n_lefts[w];
+            }
+            int done_r = s0 - lo - done_l;
+            L = R = kNoBox;
+            sah_for(in, s0, s1, lane, [&](const SahBox& b, int i, bool on) {
+                const bool left = on && goes_left(b, i);
                 const unsigned long long ml = __ballot(left), mr = __ballot(on && !left);
                 const unsigned long long below = (1ull << lane) - 1ull;
                 box_add_if(L, b.box, left);
@@ -834,15 +910,24 @@ __global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict_
                 done_l += (int)__popcll(ml);
                 done_r += (int)__popcll(mr);
             });
-            for (int x = 0; x < 3; x++)
-                for (int off = 32; off >= 1; off >>= 1) {
-                    L.lo[x] = fminf(L.lo[x], __shfl_xor(L.lo[x], off));
-                    L.hi[x] = fmaxf(L.hi[x], __shfl_xor(L.hi[x], off));
-                    R.lo[x] = fminf(R.lo[x], __shfl_xor(R.lo[x], off));
-                    R.hi[x] = fmaxf(R.hi[x], __shfl_xor(R.hi[x], off));
+            wave_union(L);
+            wave_union(R);
+            if (lane == 0)
+                for (int x = 0; x < 3; x++) {
+                    part[wave][x] = L.lo[x];
+                    part[wave][3 + x] = L.hi[x];
+                    part[wave][6 + x] = R.lo[x];
+                    part[wave][9 + x] = R.hi[x];
                 }
-            wave_fence();
-            if (lane == 0) {
+            sync();
+            if (has && sub == 0 && lane == 0) {
+                for (int w = lead + 1; w < lead + g; w++)
+                    for (int x = 0; x < 3; x++) {
+                        L.lo[x] = fminf(L.lo[x], part[w][x]);
+                        L.hi[x] = fmaxf(L.hi[x], part[w][3 + x]);
+                        R.lo[x] = fminf(R.lo[x], part[w][6 + x]);
+                        R.hi[x] = fmaxf(R.hi[x], part[w][9 + x]);
+                    }
                 const int mid = lo + n_left, node = task.z;
                 const int4 child[2] = {make_int4(lo, mid, node + 1, (level + 1) & 1),
                                        make_int4(mid, hi, node + n_left, (level + 1) & 1)};
@@ -850,15 +935,19 @@ __global__ void __launch_bounds__(kSahBlock) k_sah_top(const float4* __restrict_
                 for (int k = 0; k < 2; k++) {
                     const int size = child[k].y - child[k].x;
                     ref[k] = size == 1 ? ~sah_load(out, child[k].x).id : child[k].z;
-                    if (size > kSahSmall) list[(level + 1) & 1][atomicAdd(&count[(level + 1) & 1], 1)] = child[k];
-                    else if (size > 1) small[atomicAdd(&n_small, 1)] = child[k];
+                    if (size > kSahSmall) {
+                        list[(level + 1) & 1][atomicAdd(&count[(level + 1) & 1], 1)] = child[k];
+                        atomicMax(&largest[(level + 1) & 1], size);
+                    }
+                    if (size > 1 && size <= kSahSmall) small[atomicAdd(&n_small, 1)] = child[k];
                 }
                 node_store(nodes, node, L, R, ref[0], ref[1]);
             }
+            sync();      // `part` and the bins are free again
         }
         __threadfence_block();
         __syncthreads();
-        if (threadIdx.x == 0) count[level & 1] = 0;
+        if (threadIdx.x == 0) count[level & 1] = largest[level & 1] = 0;
         __syncthreads();
     }
     // depth of the Karras tree: dep = links followed so far, par = where they lead
@@ -965,8 +1054,13 @@ __global__ void __launch_bounds__(kSmallBlock) k_sah_small(float4* __restrict__ 
             // every lane has a plane that parts its node, but for the last centre of
             // each axis, so a node of two or more always has a finite cost
             int win = s;
-            for (int j = s + 1; j < e; j++)
-                if (w.cost[j] < w.cost[win]) win = j;
+            float least = w.cost[s];
+#pragma unroll 4
+            for (int j = s + 1; j < e; j++) {
+                const float c = w.cost[j];
+                win = c < least ? j : win;
+                least = c < least ? c : least;
+            }
             const bool split = e - s > 1;
             const int n_left = split ? w.left[win] : 0, ax = split ? w.axis[win] : 0;
             const Box wb = w.box[split ? win : lane];
@@ -1040,11 +1134,11 @@ __device__ __forceinline__ void report_depth(int deepest, BuildState* __restrict
 }
 
 // The first levels, one block after another's barrier instead of a launch each,
-// until a level has more nodes than the block has threads.  Level l's list is
+// until a level has more than `most` nodes.  Level l's list is
 // lists + (l & 1) n_int.
 constexpr int kTopBlock = 1024;
 __global__ void __launch_bounds__(kTopBlock) k_wide_top(const float4* __restrict__ nodes, int64_t n_int,
-                                                        int2* lists, unsigned* __restrict__ flags,
+                                                        int most, int2* lists, unsigned* __restrict__ flags,
                                                         BuildState* __restrict__ st, bool depth) {
     __shared__ int n_next;
     int deepest = 0, count = 1, level = 0;
@@ -1053,7 +1147,7 @@ __global__ void __launch_bounds__(kTopBlock) k_wide_top(const float4* __restrict
         flags[0] = 1u;
         st->count[0] = 1;
     }
-    while (count > 0 && count <= kTopBlock && level < kMaxLevels) {
+    while (count > 0 && count <= most && level < kMaxLevels) {
         if (threadIdx.x == 0) n_next = 0;
         __threadfence_block();
         __syncthreads();
@@ -1263,8 +1357,11 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
     // after 8 passes (or none) the sorted data is back in (morton, v0)
     hipLaunchKernelGGL(k_gather, dim3(g), dim3(kBlock), 0, st, V, n_v, F, va, M, n, s->tris, s->normals, boxes);
     constexpr int kLevelBatch = 16, kTopLevels = 5;      // k_wide_top takes levels 0..4 at least (4^5 nodes)
-    // no level of so few triangles has more nodes than k_wide_top takes
-    int level = n <= 2 * kTopBlock ? kMaxLevels : kTopLevels;
+    // no level of so few triangles has more nodes than k_wide_top takes (each holds
+    // two triangles at least), and up to 4096 triangles two per thread cost less than
+    // the launches (16, 71 us)
+    const int most = n <= 4 * kTopBlock ? 2 * kTopBlock : kTopBlock;
+    int level = n <= 2 * most ? kMaxLevels : kTopLevels;
     int64_t wide_cap = (int64_t)(wide_bytes / wide_node);
     auto queue_levels = [&]() {
         const unsigned gl = std::min(g, 512u);
@@ -1294,7 +1391,7 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
             hipLaunchKernelGGL(k_sah_small, dim3((unsigned)std::min<int64_t>(256, (n + 31) / 32)), dim3(kSmallBlock), 0, st,
                                (float4*)tree, buf, buf + 2 * n, small, state);
         }
-        hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, tree, n_int, lists, flags, state, !sah);
+        hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, tree, n_int, most, lists, flags, state, !sah);
         queue_levels();
         queue_emit((float4*)(base + o_wide), wide_cap);
     }
@@ -1322,7 +1419,7 @@ rt_status rt_build_lbvh(rt_scene* s, const float* V, int64_t n_v, const int32_t*
             }
             const int upto = level + kLevelBatch;
             hipLaunchKernelGGL(k_build_init, dim3(std::min(g, 1024u)), dim3(kBlock), 0, st, state, flags, n_int);
-            hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, tree, n_int, lists, flags, state, !sah);
+            hipLaunchKernelGGL(k_wide_top, dim3(1), dim3(kTopBlock), 0, st, tree, n_int, most, lists, flags, state, !sah);
             level = kTopLevels;
             while (level < std::min(upto, kMaxLevels)) queue_levels();
             queue_emit((float4*)(base + o_wide), wide_cap);
