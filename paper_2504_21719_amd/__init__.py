@@ -126,6 +126,20 @@ def _check(status):
         raise RtError(status, lib().rt_last_error().decode(errors="replace"))
 
 
+def _check_alloc(fn, *args):
+    """Calls an entry point that allocates device memory.  Where the driver
+    refuses, once more after torch's allocator has given back what it keeps
+    unused: the tapes of the autograd function stay there for the next one, and
+    without this a scene or a tape that fits the card would be refused.  (Such
+    a call fails before it has queued anything that writes an output.)"""
+    status = fn(*args)
+    if status == RT_ENOMEM:
+        import torch
+        torch.cuda.empty_cache()
+        status = fn(*args)
+    _check(status)
+
+
 def _stream(stream=None):
     import torch
     if stream is None:
@@ -276,7 +290,7 @@ def rt_build_scene(vertices, triangles, tri_material, n_materials, stream=None) 
     pv, pf, pm = _ptrs((vertices, "vertices", torch.float32, 3 * n_v), (triangles, "triangles", torch.int32, 3 * n_t),
                        (tri_material, "tri_material", torch.int32, n_t))
     h = C.c_void_p()
-    _check(lib().rt_build_scene(pv, n_v, pf, n_t, pm, int(n_materials), _stream(stream), C.byref(h)))
+    _check_alloc(lib().rt_build_scene, pv, n_v, pf, n_t, pm, int(n_materials), _stream(stream), C.byref(h))
     return RtScene(h, int(n_materials))
 
 
@@ -373,7 +387,7 @@ class RtTape:
 def rt_tape_create(params, **pkw) -> RtTape:
     p = params if isinstance(params, rt_sbr_params) else make_params(params, **pkw)
     h = C.c_void_p()
-    _check(lib().rt_tape_create(C.byref(p), C.byref(h)))
+    _check_alloc(lib().rt_tape_create, C.byref(p), C.byref(h))
     return RtTape(h, int(lib().rt_tape_bytes(C.byref(p))))
 
 
@@ -411,8 +425,8 @@ def rt_radio_map_backward(scene: RtScene, eps_r, sigma, tx, plane, params, tape:
                 _f32spec(grad_orient, "grad_orient", 3))
     t = tx if isinstance(tx, rt_tx) else make_tx(tx)
     fn = lib().rt_radio_map_backward_noalloc if noalloc else lib().rt_radio_map_backward
-    _check(fn(scene.handle, rt_materials(*ptr[:6]), C.byref(t), C.byref(pl), C.byref(p),
-              tape.handle, *ptr[6:], _stream(stream)))
+    _check_alloc(fn, scene.handle, rt_materials(*ptr[:6]), C.byref(t), C.byref(pl), C.byref(p),
+                 tape.handle, *ptr[6:], _stream(stream))
 
 
 def rt_radio_map_batched(scene: RtScene, eps_r, sigma, txs: Sequence, rays_per_tx: Sequence[int], plane, params,
@@ -440,8 +454,8 @@ def rt_radio_map_batched(scene: RtScene, eps_r, sigma, txs: Sequence, rays_per_t
     descs = [tx if isinstance(tx, rt_tx) else make_tx(tx) for tx in txs]
     arr = (rt_tx * n_tx)(*descs)
     budgets = (C.c_int64 * n_tx)(*[int(b) for b in rays_per_tx])
-    _check(lib().rt_radio_map_batched(scene.handle, mats, S, arr, C.cast(budgets, C.c_void_p),
-                                      n_tx, C.byref(pl), C.byref(p), *ptrs, _stream(stream)))
+    _check_alloc(lib().rt_radio_map_batched, scene.handle, mats, S, arr, C.cast(budgets, C.c_void_p),
+                 n_tx, C.byref(pl), C.byref(p), *ptrs, _stream(stream))
     del descs
     return out_maps
 

@@ -21,6 +21,7 @@ rt_status rt_fail(rt_status st, const std::string& m) {
     return st;
 }
 rt_status rt_hip_fail(hipError_t e, const char* what) {
+    (void)hipGetLastError();     // reported here, not once more by the next launch's check
     g_err = std::string(what) + ": " + hipGetErrorString(e);
     return e == hipErrorOutOfMemory ? RT_ENOMEM : RT_EDEVICE;
 }
