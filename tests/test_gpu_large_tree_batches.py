@@ -1,5 +1,6 @@
 """Batched calls on a tree larger than an L2 against single ones: several
-transmitters that go through stretches of their lattices at once."""
+transmitters that go through stretches of their lattices at once, and one whose
+first units are of 16 rays."""
 import numpy as np
 import pytest
 
@@ -44,3 +45,23 @@ def _compare(terrain, budgets, samples, depth=2):
 @pytest.mark.parametrize("budgets", [[50_000] * 24, [2 * LANES + 5, 2 * LANES, LANES + 7], [LANES // 3] * 13 + [999]])
 def test_several_transmitters(terrain, budgets, samples):
     _compare(terrain, budgets, samples)
+
+
+@pytest.mark.parametrize("samples", [1, 2])
+@pytest.mark.parametrize("n", [LANES // 2 + 9, 2 * LANES + 1, 5 * LANES - 77])
+def test_one_transmitter(terrain, n, samples):
+    _compare(terrain, [n], samples)
+
+
+@pytest.mark.parametrize("refill", [8, 48, 64])
+def test_first_units_and_refills(terrain, refill):
+    """Whatever the refill threshold, the narrow first units hand out every ray."""
+    rt, torch, cfg, scene, eps, sig = terrain
+    n = 2 * LANES + 333
+    rt.rt_set_launch_config(scene, refill=refill)
+    hits = torch.full((n, 1), -7, dtype=torch.int32, device="cuda")
+    stats = torch.zeros(8, dtype=torch.int64, device="cuda")
+    out = torch.empty((1, cfg.plane.H, cfg.plane.W), dtype=torch.float32, device="cuda")
+    rt.rt_radio_map(scene, eps, sig, cfg.tx, cfg.plane, sg.Params(3.5e9, n, 0), out, hits=hits, stats=stats)
+    rt.rt_set_launch_config(scene)
+    assert not bool((hits == -7).any()) and not bool((hits == -2).any()) and int(stats[0]) == n
