@@ -1179,8 +1179,13 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
     // (whose lanes wait less for each other), at least 8 rays wide; not where
     // every triangle is tested, for as long on each lane (5,810 triangles, 2e4
     // rays: 11.4 ms with 8 rays per wavefront, 8.6 with 64)
+    // Nor on a map of so few cells that every wavefront adds to the same ones (25 ns
+    // each on one address), in a scene of so few triangles that this takes longer
+    // than its rays (14 triangles, 1 to 64 cells, 2e4 rays 48 -> 23 us, 1e5 54 ->
+    // 36; city, 1 cell: 2e4 rays would take 108 us instead of 101).
+    const bool crowded = a.tape_groups == 4 && a.map_stride <= 256 && s->n_wide < 32;
     a.width = 64;
-    while (!brute && a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
+    while (!brute && !crowded && a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
     a.n_units = (a.n_work + a.width - 1) / a.width;
     // one transmitter on a large tree, with room for narrow first units on both
     // sides of the equator
@@ -1218,6 +1223,10 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
         if (a.tape_groups == 4 && a.n_units >= 4 * waves) {
             if (a.deposit == RT_DEPOSIT_ATOMIC) n_stretch = 16;
             else if (order.chunk == 0) n_stretch = a.n_tx > 0 ? 8 : 1;
+            // a map of a few cells (5,810 triangles, 1 cell, 4e6 rays 855 -> 766 us, 1e7
+            // 1.97 -> 1.74 ms; from 64 cells on, and on the 1.02 M-triangle scene, one
+            // front is as fast or faster)
+            else if (a.map_stride < 32 && s->n_wide < kLargeTree) n_stretch = 4;
         }
         // and where the transmitters' horizons would follow one another
         if (!n_stretch && a.n_tx > 1 && s->n_wide >= kLargeTree && a.n_units >= 4 * waves &&

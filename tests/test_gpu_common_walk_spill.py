@@ -24,7 +24,7 @@ def _scene(kind):
     """Scenes of more than 4096 triangles (smaller ones have a shallower tree) whose
     boxes are large and seldom hit, so that children stay deferred.  Counted with a
     counter in the kernel, 4,099 rays push 226 k entries to the spill area in
-    `slivers` and 1e5 rays 5 k lanes' worth in `nested`, where two wavefronts also
+    `slivers` and 1e5 rays 2.9 M in `nested`, where two wavefronts also
     hand over to the per-lane loop with entries there."""
     rng = np.random.default_rng(1)
     if kind == "slivers":                  # thin triangles through the whole volume

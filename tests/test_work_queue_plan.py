@@ -22,7 +22,7 @@ int64_t rt_order_chunk(const LaunchOrder&) { return g_chunk; }
 rt_status rt_fail(rt_status st, const std::string&) { return st; }
 static FwdArgs g_args;
 struct Call {       // what a launch passes to size_launch, and what it gets
-    int64_t n_work, lattice, begin, chunk, n_wide;
+    int64_t n_work, lattice, begin, chunk, n_wide, cells;
     int32_t cu, block, n_tx, deposit, refill, brute;
     int64_t blocks, once, width, nq, claim, n_units, n_claim, per_queue, n_first, first_width, spread;
 };
@@ -41,6 +41,7 @@ extern "C" int plan(Call* c) {
     a.deposit = c->deposit;
     a.refill = c->refill;
     a.tape_groups = 4;
+    a.map_stride = c->cells;
     LaunchOrder order{0, c->chunk > 1 ? 10 : 0, 0};
     int blocks = 0;
     const int st = SIZE_LAUNCH;
@@ -72,7 +73,7 @@ extern "C" void hand_out(unsigned char* seen) {
 
 
 class Call(C.Structure):
-    _fields_ = ([(n, C.c_int64) for n in ("n_work", "lattice", "begin", "chunk", "n_wide")] +
+    _fields_ = ([(n, C.c_int64) for n in ("n_work", "lattice", "begin", "chunk", "n_wide", "cells")] +
                 [(n, C.c_int32) for n in ("cu", "block", "n_tx", "deposit", "refill", "brute")] +
                 [(n, C.c_int64) for n in ("blocks", "once", "width", "nq", "claim", "n_units", "n_claim", "per_queue",
                                           "n_first", "first_width", "spread")])
@@ -102,9 +103,9 @@ def lib(tmp_path_factory):
 
 
 def _plan(lib, n_work, cu=256, block=256, n_tx=0, chunk=987, n_wide=100, begin=0, lattice=None, deposit=2, refill=64,
-          brute=0):
+          brute=0, cells=10_000):
     c = Call(n_work=n_work, lattice=lattice or n_work, begin=begin, chunk=chunk, n_wide=n_wide, cu=cu, block=block,
-             n_tx=n_tx, deposit=deposit, refill=refill, brute=brute)
+             n_tx=n_tx, deposit=deposit, refill=refill, brute=brute, cells=cells)
     assert lib.plan(C.byref(c)) == 0
     return c
 
@@ -203,3 +204,21 @@ def test_horizons_of_several_transmitters(lib, n_tx):
             assert (c.spread == 4) == (units < min(64, 8 * n_tx))
         _every_index_once(lib, c)
         assert not _plan(lib, n, 4, n_tx=n_tx, n_wide=30_000).spread
+
+
+@pytest.mark.parametrize("n_tx", [0, 1, 3])
+def test_maps_of_few_cells(lib, n_tx):
+    """Wavefronts that add to the same cells: whole ones in small calls on a small
+    scene, stretches in large calls."""
+    for cells in (1, 31, 32, 256, 257):
+        for n in (1, 900, LANES // 4 + 3):
+            for n_wide in (5, 31, 32, 300):
+                c = _plan(lib, n, 4, n_tx=n_tx, n_wide=n_wide, cells=cells)
+                assert (c.width == 64) == (cells <= 256 and n_wide < 32)
+                _every_index_once(lib, c)
+        n = 9 * LANES + 77
+        for n_wide in (5, 300, 40_000):
+            c = _plan(lib, n, 4, n_tx=n_tx, n_wide=n_wide, cells=cells)
+            if n_wide < 32_768:
+                assert (c.spread == 4) == (cells < 32)
+            _every_index_once(lib, c)
