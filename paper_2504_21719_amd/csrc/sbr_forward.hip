@@ -174,7 +174,10 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // last near the call's end; in calls of up to 64 units per wavefront in all and
 // 8 per transmitter four stretches per queue spread them (64 transmitters of 5e4
 // rays 1.40 -> 1.10 ms, 16 of 3e5 1.51 -> 1.24, 64 of 2e5 3.74 -> 3.40; larger
-// calls lose: 32 of up to 2e6 rays 6.4 -> 7.4, 3 of 3e6 1.67 -> 1.80).
+// calls lose: 32 of up to 2e6 rays 6.4 -> 7.4, 3 of 3e6 1.67 -> 1.80).  Below
+// four units per wavefront one stretch per queue does for four transmitters and
+// more (8 of 1e5 605 -> 535 us, 16 of 5e4 589 -> 549, 4 of 7e4 503 -> 438; 2 of
+// 3e5 would take 606 instead of 512).
 __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
     *first = *end = 0;
     if (i < a.n_first) {
@@ -1229,9 +1232,10 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
             else if (a.map_stride < 32 && s->n_wide < kLargeTree) n_stretch = 4;
         }
         // and where the transmitters' horizons would follow one another
-        if (!n_stretch && a.n_tx > 1 && s->n_wide >= kLargeTree && a.n_units >= 4 * waves &&
-            a.n_units <= waves * std::min(64, 8 * a.n_tx))
-            n_stretch = 4;
+        if (!n_stretch && a.n_tx > 1 && s->n_wide >= kLargeTree && a.n_units <= waves * std::min(64, 8 * a.n_tx)) {
+            if (a.n_units >= 4 * waves) n_stretch = 4;
+            else if (a.n_tx >= 4) n_stretch = 1;
+        }
         const int64_t turn = (int64_t)a.nq * std::max(1u, n_stretch);
         const int64_t narrow = a.n_tx > 1 && !n_stretch ? 32 * waves * a.width : 0;     // indices left to units of one wavefront
         if (a.n_tx > 1) {

@@ -42,7 +42,8 @@ def _compare(terrain, budgets, samples, depth=2):
 
 
 @pytest.mark.parametrize("samples", [1, 2])
-@pytest.mark.parametrize("budgets", [[50_000] * 24, [2 * LANES + 5, 2 * LANES, LANES + 7], [LANES // 3] * 13 + [999]])
+@pytest.mark.parametrize("budgets", [[50_000] * 24, [2 * LANES + 5, 2 * LANES, LANES + 7], [LANES // 3] * 13 + [999],
+                                     [LANES // 3] * 5, [LANES // 2 + 1] * 3])
 def test_several_transmitters(terrain, budgets, samples):
     _compare(terrain, budgets, samples)
 

@@ -55,7 +55,7 @@ extern "C" int plan(Call* c) {
     c->per_queue = (int64_t)a.per_queue;
     c->n_first = a.n_first;
     c->first_width = a.first_width;
-    c->spread = a.by_r == 1 && a.by_k != 1 ? a.run : 0;
+    c->spread = a.by_r == 1 && a.by_k == a.nq * a.by_q ? a.run : 0;
     return st;
 }
 // work of entry i of queue q, of the last plan
@@ -194,14 +194,14 @@ def test_stretches(lib, monkeypatch, n_tx, queues, claim):
         assert c.spread == 16 and c.per_queue < 2 ** 32 and c.n_claim * c.nq >= c.n_units
 
 
-@pytest.mark.parametrize("n_tx", [2, 3, 16, 64])
+@pytest.mark.parametrize("n_tx", [2, 3, 4, 16, 64])
 def test_horizons_of_several_transmitters(lib, n_tx):
     """On a large tree the transmitters of middling calls go through stretches."""
-    for units in (4, 7, 15, 17, 30, 63, 65):
+    for units in (1, 2, 3, 4, 7, 15, 17, 30, 33, 63, 65):
         n = units * LANES + 77
         c = _plan(lib, n, 4, n_tx=n_tx, n_wide=40_000)
-        if n > 2 * 4096 + LANES:                     # some turns of 4 stretches on 16 queues
-            assert (c.spread == 4) == (units < min(64, 8 * n_tx))
+        few = 1 if n_tx >= 4 else 0
+        assert c.spread == (few if units < 4 else 4 if units < min(64, 8 * n_tx) else 0)
         _every_index_once(lib, c)
         assert not _plan(lib, n, 4, n_tx=n_tx, n_wide=30_000).spread
 
