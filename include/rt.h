@@ -52,7 +52,8 @@
  *     RTMAP_WIDTH (2: binary tree, else 4-wide), RTMAP_ORDER (0: lattice
  *     launch order, else coherent), RTMAP_REFILL (idle lanes a wavefront
  *     waits for before it takes new rays, 1..64), RTMAP_QUEUES (number of
- *     work queues, 1..32), RTMAP_CLAIM (rays per claim, 64..4096),
+ *     work queues, 1..32), RTMAP_CLAIM (rays per claim, 64..4096; more in
+ *     calls of over 2^30 claims),
  *     RTMAP_NO_GRAPH (set: rt_radio_map_batched launches its kernels instead
  *     of replaying the captured graph).  They override rt_tune's choice and
  *     rt_set_launch_config.
@@ -146,7 +147,10 @@ rt_status rt_scene_info_get(const rt_scene* scene, rt_scene_info* out);
  *                                   (>= 0 wide node, < 0 leaf slot ~r,
  *                                   0x7fffffff empty), then the leaf mask as
  *                                   int bits (bit c + 1: child c is a leaf) and
- *                                   three unused; node 0 is the root
+ *                                   three unused; node 0 is the root.  Scenes
+ *                                   of up to 4096 triangles take them from
+ *                                   another binary tree than `nodes`, over
+ *                                   the same slots
  *   tris    float  [n_triangles][12] triangles in slot order: (v0, original
  *                                   id bits), (v1, material bits), (v2, 0)
  *   n_wide  out (may be NULL): number of 4-wide nodes, 0 if the scene has no
@@ -271,7 +275,8 @@ enum { RT_DEPOSIT_AUTO = 0, RT_DEPOSIT_ATOMIC = 1, RT_DEPOSIT_WAVE = 2 };
  *   t_min       spawned rays accept hits at t > t_min (metres); the triangle
  *               just hit is always excluded
  *   accel       RT_ACCEL_BVH (tuned tree width), RT_ACCEL_BVH2 (binary LBVH),
- *               RT_ACCEL_BVH4 (4-wide tree collapsed from it), or
+ *               RT_ACCEL_BVH4 (4-wide tree, collapsed from it or, in scenes of
+ *               up to 4096 triangles, from a tree split by surface area), or
  *               RT_ACCEL_BRUTE (every triangle is tested with the same
  *               intersection test, for validation).  All four give
  *               identical hits.
@@ -486,8 +491,9 @@ rt_status rt_radio_map_batched(const rt_scene* scene, rt_materials materials,
  * Writes the chosen block size and deposit strategy (host ints, may be NULL);
  * rt_scene_info_get reports the whole choice.
  * Launch order: by default each chunk of consecutive lattice indices (a
- * Fibonacci number of them) is launched sorted by azimuth, so that a wavefront starts on a small patch of
- * directions (results are unchanged up to FP32 summation order).
+ * Fibonacci number of them) is launched sorted by azimuth, so that a wavefront
+ * starts on a small patch of directions (results are unchanged up to FP32
+ * summation order).
  * Synchronises `stream`; `scratch_map` is device float32 of the map's size
  * and is overwritten.
  */

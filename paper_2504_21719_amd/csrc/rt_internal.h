@@ -51,7 +51,8 @@ struct rt_scene {
     float4* nodes = nullptr;
     float4* tris = nullptr;
     float4* normals = nullptr;
-    // 4-wide BVH collapsed from the binary one: 8 x float4 (128 B) per node,
+    // 4-wide BVH, collapsed from the binary one or, for few triangles, from a
+    // second binary tree that is not kept: 8 x float4 (128 B) per node,
     //   w0 = x_lo of children 0..3, w1 = x_hi, w2 = y_lo, w3 = y_hi,
     //   w4 = z_lo, w5 = z_hi, w6 = child refs (>= 0 wide node, < 0 leaf
     //   slot ~r, RT_WIDE_EMPTY), w7.x = leaf mask (int bits, bit c + 1 for
@@ -66,8 +67,8 @@ struct rt_scene {
     size_t bytes = 0;
     double build_ms = 0.0;
     float lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
-    // per-scene workspace: RT_QUEUES work-queue heads and the drained-queue
-    // count, RT_QUEUE_STRIDE apart
+    // per-scene workspace: RT_QUEUES work-queue heads and the mask of drained
+    // queues, RT_QUEUE_STRIDE apart
     unsigned long long* counters = nullptr;
     int* spill = nullptr;     // traversal stack spill
     size_t spill_entries = 0; // ints available in `spill`

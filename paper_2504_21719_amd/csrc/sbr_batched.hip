@@ -2,8 +2,8 @@
 //
 // Work over all transmitters is one index space: transmitter t owns the
 // global ray indices [prefix[t], prefix[t+1]) (ordered largest budget first,
-// so long lattices start early), and lanes of the persistent kernel pull
-// indices from one device counter, whatever transmitter they belong to.
+// so long lattices start early), and wavefronts of the persistent kernel take
+// units of it from the work queues, whatever transmitter they belong to.
 //
 //  * one material set, forward only: a single persistent launch traces,
 //    reflects and deposits into the map of each ray's transmitter;
@@ -322,8 +322,8 @@ __global__ void __launch_bounds__(kSampBlock) k_samples(const SampArgs a) {
             if (GRAD) {
                 // one partial sum per (transmitter, 64-ray group, sample,
                 // parameter), summed later in a fixed order: the lanes of each
-                // transmitter in this group (usually one) are summed with a
-                // butterfly and their leader stores the sums in that
+                // transmitter in this group (usually one) are summed by
+                // data-parallel primitives and lane 63 stores the sums in that
                 // transmitter's entry for this group
                 const int64_t gw = g0 >> 6;
                 unsigned long long pend = __ballot(valid);

@@ -257,7 +257,7 @@ __device__ __forceinline__ void sincos_quarter_turns(double v, float& s, float& 
 // (Sec. "Handling Multiple Transmit Antennas"): alpha = a_tx^T u_P with the
 // array response a_tx[i] = exp(j 2 pi/lambda k.d_i) of
 // eq. path-solver-array-response-vector.  The phase is formed in FP64 in
-// quarter turns; the element data are the same for every lane.  VALU-bound, 32
+// quarter turns; the element data are the same for every lane.  VALU-bound, 33
 // instructions per element (49 before: the direction is scaled once per ray, the
 // quadrant comes from the rounded sum's bits instead of a 64-bit conversion and
 // three compares, there is no division), with the elements read through the

@@ -168,7 +168,12 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // the wavefronts at the horizon: in calls of up to six units per wavefront the
 // first units, nearest the equator, are then of 16 rays (1.02 M triangles, 9e4
 // rays 416 -> 378 us, 2e5 554 -> 397, 4e5 501 -> 376, 1e6 547 -> 477, 4e6 would
-// take 8 % more; the city would at 1e6 rays too, its fetches being short).
+// take 8 % more; the city would at 1e6 rays too, its fetches being short).  On
+// smaller trees it depends on the scene: boxes on a ground of 19,202 triangles would
+// gain at 2e5 rays (208 -> 172 us) and lose at 1.4e6 (218 -> 272), 49,154
+// likewise (183 -> 163, 218 -> 267), 20,000 loose triangles lose throughout (2e5
+// 779 -> 944).  With a refill threshold of 48 or less the lanes left idle refill after
+// one segment: 1e6 rays gain 8 instead of 10 %, 1.4e6 nothing instead of 5.
 //
 // Several transmitters on such a tree have their horizons one after another, the
 // last near the call's end; in calls of up to 64 units per wavefront in all and
@@ -1275,7 +1280,6 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
     const int64_t rest = std::max<int64_t>(0, a.n_work - a.hole_size - (int64_t)a.n_claim * a.nq * a.claim);
     a.per_queue = (unsigned long long)a.n_first + a.n_claim + (unsigned long long)((rest + (int64_t)a.width * a.nq - 1) / ((int64_t)a.width * a.nq));
     const int64_t threads = blocks * block;
-    // a wide traversal pushes up to 3 entries per wide level (= 2 binary levels)
     int64_t need_depth = std::max<int64_t>(0, rt_stack_need(s) - RT_STACK_LDS);
     if ((int64_t)s->spill_entries < need_depth * threads)
         return rt_fail(RT_EOVERFLOW, "traversal spill area too small for this launch");

@@ -648,10 +648,13 @@ __device__ __forceinline__ int wide_children(const float4* __restrict__ nodes, i
 // to a single house's: on the city (1202 triangles, ground of 2) a segment
 // visits 7.5 wide nodes of the Karras tree and 5.0 of this one.  Maps of 1e6 and
 // 1e7 rays 162 -> 135 and 618 -> 539 us, 64 rooftop transmitters 6.3 -> 5.3 ms;
-// in the build k_sah_top takes 127 and k_sah_small 59 us.  Larger scenes are
-// left out because one workgroup makes the upper splits: at 3890 triangles the two
-// take 350 us, twice what a map of 1e6 rays gains.  The 1.02 M-triangle terrain,
-// whose triangles are alike, would be visited 9 % less.
+// in the build k_sah_top takes 127 and k_sah_small 59 us.  The line at 4096 is
+// what one workgroup makes in reasonable time, not where the tree stops to gain:
+// boxes on a ground of 4,334, 5,810 and 8,114 triangles would build in 802, 904 and
+// 1036 us instead of 396, 399 and 407 and trace maps of 1e6 rays in 379, 162 and
+// 190 us instead of 406, 216 and 245 (1e7: 1.74, 0.93, 0.98 ms instead of 2.15, 1.16,
+// 1.24), so that a scene kept for some ten such maps would gain.  The 1.02
+// M-triangle terrain, whose triangles are alike, would be visited 9 % less.
 //
 // Node numbers are those of a depth-first walk: the left child of node i is
 // i + 1, the right one i + (leaves on the left); triangle order within a node
