@@ -157,9 +157,9 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // lattice order, whose wavefronts hold no neighbours), calls of four units per
 // wavefront and more go through several stretches at once instead, one per
 // queue and turn (against one front, and in brackets the contiguous ranges on 256
-// queues; city: lattice order, 5e6 rays 1.60 -> 1.14 ms [1.23], 2e7 6.5 -> 4.5
-// [4.5]; atomics, 2e6 0.55 -> 0.45 [0.48], 5e6 1.57 -> 1.20 [1.20], 2e7 5.6 -> 4.7
-// [5.6]; three transmitters of 3e6 rays 3.9 -> 1.9 [2.1] and 4.4 -> 2.8 [3.5]).
+// queues; city: lattice order, 5e6 rays 1.66 -> 1.13 ms [1.22], 2e7 6.56 -> 4.45
+// [4.51]; atomics, 2e6 0.53 -> 0.45 [0.48], 5e6 1.45 -> 1.20 [1.21], 2e7 6.09 ->
+// 4.74 [5.28]; three transmitters of 3e6 rays 3.6 -> 1.9 [2.1] and 4.6 -> 3.1 [3.4]).
 // Few stretches suffice in lattice order, where the 1.02 M-triangle scene would
 // lose 10 % at 1.5e6 rays with 16; atomics take 16 (with 4 the city's 1.1e6 rays
 // take 0.33 ms, with 16 0.27).
@@ -178,10 +178,10 @@ __device__ __forceinline__ int find_tx(const int64_t* __restrict__ prefix, int n
 // Several transmitters on such a tree have their horizons one after another, the
 // last near the call's end; in calls of up to 64 units per wavefront in all and
 // 8 per transmitter four stretches per queue spread them (64 transmitters of 5e4
-// rays 1.40 -> 1.10 ms, 16 of 3e5 1.51 -> 1.24, 64 of 2e5 3.74 -> 3.40; larger
-// calls lose: 32 of up to 2e6 rays 6.4 -> 7.4, 3 of 3e6 1.67 -> 1.80).  Below
+// rays 1.40 -> 1.10 ms, 16 of 3e5 1.50 -> 1.24; larger calls lose: 32 of up to
+// 2e6 rays 6.4 -> 7.4, 3 of 3e6 1.67 -> 1.80).  Below
 // four units per wavefront one stretch per queue does for four transmitters and
-// more (8 of 1e5 605 -> 535 us, 16 of 5e4 589 -> 549, 4 of 7e4 503 -> 438; 2 of
+// more (8 of 1e5 599 -> 541 us, 16 of 5e4 594 -> 558, 4 of 7e4 512 -> 434; 2 of
 // 3e5 would take 606 instead of 512).
 __device__ __forceinline__ void queue_entry(const FwdArgs& a, unsigned i, int q, int64_t* first, int64_t* end) {
     *first = *end = 0;
@@ -1186,11 +1186,11 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
     // fewer rays than the resident wavefronts have lanes: narrower wavefronts
     // (whose lanes wait less for each other), at least 8 rays wide; not where
     // every triangle is tested, for as long on each lane (5,810 triangles, 2e4
-    // rays: 11.4 ms with 8 rays per wavefront, 8.6 with 64)
+    // rays: 11.4 ms with 8 rays per wavefront, 8.6 with 64).
     // Nor on a map of so few cells that every wavefront adds to the same ones (25 ns
     // each on one address), in a scene of so few triangles that this takes longer
-    // than its rays (14 triangles, 1 to 64 cells, 2e4 rays 48 -> 23 us, 1e5 54 ->
-    // 36; city, 1 cell: 2e4 rays would take 108 us instead of 101).
+    // than its rays (14 triangles, 1 cell, 2e4 rays 46 -> 20 us, 1e5 52 ->
+    // 33; city, 1 cell: 2e4 rays would take 108 us instead of 101).
     const bool crowded = a.tape_groups == 4 && a.map_stride <= 256 && s->n_wide < 32;
     a.width = 64;
     while (!brute && !crowded && a.width > 8 && a.n_work <= (waves - 7) * (a.width / 2)) a.width /= 2;
@@ -1231,8 +1231,8 @@ static rt_status size_launch(FwdArgs& a, const rt_scene* s, int block, const Lau
         if (a.tape_groups == 4 && a.n_units >= 4 * waves) {
             if (a.deposit == RT_DEPOSIT_ATOMIC) n_stretch = 16;
             else if (order.chunk == 0) n_stretch = a.n_tx > 0 ? 8 : 1;
-            // a map of a few cells (5,810 triangles, 1 cell, 4e6 rays 855 -> 766 us, 1e7
-            // 1.97 -> 1.74 ms; from 64 cells on, and on the 1.02 M-triangle scene, one
+            // a map of a few cells (5,810 triangles, 1 cell, 4e6 rays 853 -> 773 us, 1e7
+            // 1.98 -> 1.76 ms; from 64 cells on, and on the 1.02 M-triangle scene, one
             // front is as fast or faster)
             else if (a.map_stride < 32 && s->n_wide < kLargeTree) n_stretch = 4;
         }
